@@ -395,7 +395,10 @@ int ppo_fused_shape(const ppo_ctx *ctx, int32_t *rows, int32_t *threads);
 /* The same for bf16 inference (ppo_rollout_infer): without PPO_FUSED_ROWS /
  * PPO_FUSED_THREADS it prefers 32 rows x 256 threads (two workgroups per
  * CU): a policy step over a few thousand environments is latency-bound, and
- * more, shorter workgroups finish it sooner.  Host only. */
+ * more, shorter workgroups finish it sooner.  Both 0 also for networks outside
+ * this block that inference runs in a single launch of another one (narrow
+ * widths such as [64, 64], wide first layers such as [1024, 512, 256], input
+ * widths that are no multiple of 16).  Host only. */
 int ppo_fused_infer_shape(const ppo_ctx *ctx, int32_t *rows, int32_t *threads);
 
 /* Terrain seen by the height scan: a height field on a uniform grid and the

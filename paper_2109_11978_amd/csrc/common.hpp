@@ -220,6 +220,9 @@ struct FusedShape {
 // inference's).
 FusedShape fused_shape(int L, const int *H, int kpad, int A, int prefer_rows = 0, int prefer_threads = 0,
                        bool update = false, int prefer_per_cu = 0);
+// Shape of a rollout inference launch: that of fused_shape, else a narrow
+// network's or the wide pass's (only without preferences).
+FusedShape fused_infer_shape(int L, const int *H, int kpad, int A, int prefer_rows, int prefer_threads);
 int fused_blocks(int M, int R);
 hipError_t launch_fused_update(FusedArgs a, hipStream_t s);
 // Forward pass and sampling head for M environments (rows of obs in order).

@@ -128,6 +128,7 @@ struct WsPlan {
     // rows of the GEMM chain
     int rows = 0;
     int kpad = 0;      // padded observation width of the gathered input
+    int kfrag = 0;     // the same in whole k-steps of 16 (first-layer fragments)
     size_t esz = 4;    // bytes per activation element
     Region xg;
     Region h_a[kMaxHidden], h_c[kMaxHidden];
@@ -214,6 +215,7 @@ WsPlan plan_workspace(const NetLayout &g, Precision prec, int N, int T, int M) {
     WsPlan w;
     w.esz = prec == kBF16 ? 2 : 4;
     w.kpad = static_cast<int>(align_up(g.D, 8));
+    w.kfrag = static_cast<int>(align_up(g.D, 16));
     const int rows = std::max(N, M);
     w.rows = rows;
     Alloc a;
@@ -263,12 +265,12 @@ WsPlan plan_workspace(const NetLayout &g, Precision prec, int N, int T, int M) {
         }
     w.wt = a.take(std::max<size_t>(wt_elems, 1) * w.esz);
     size_t frag_elems = 0;
-    if (prec == kBF16 && w.kpad % 16 == 0) {
+    if (prec == kBF16) {
         for (int net = 0; net < 2; ++net)
             for (int l = 0; l < g.L; ++l) {
                 w.frag_w[net][l] = frag_elems;
                 // the critic's forward fragments in the split layout (twice the size)
-                frag_elems += static_cast<size_t>(g.H[l]) * (l == 0 ? w.kpad : g.H[l - 1]) * (net == 1 ? 2 : 1);
+                frag_elems += static_cast<size_t>(g.H[l]) * (l == 0 ? w.kfrag : g.H[l - 1]) * (net == 1 ? 2 : 1);
                 if (l >= 1) {
                     w.frag_wt[net][l] = frag_elems;
                     frag_elems += static_cast<size_t>(g.H[l - 1]) * g.H[l];
@@ -1009,8 +1011,10 @@ FusedShape fused_shape_for(const ppo_ctx *c, const ppo_params *p, const WsPlan &
     const char *rows = std::getenv("PPO_FUSED_ROWS");
     const char *threads = std::getenv("PPO_FUSED_THREADS");
     const char *per_cu = inference ? nullptr : std::getenv("PPO_FUSED_PER_CU");
-    FusedShape sh = fused_shape(g.L, g.H, w.kpad, g.A, rows ? std::atoi(rows) : 0, threads ? std::atoi(threads) : 0,
-                                !inference, per_cu ? std::atoi(per_cu) : 0);
+    const int want_r = rows ? std::atoi(rows) : 0, want_t = threads ? std::atoi(threads) : 0;
+    const FusedShape sh = inference ? fused_infer_shape(g.L, g.H, w.kfrag, g.A, want_r, want_t)
+                                    : fused_shape(g.L, g.H, w.kpad, g.A, want_r, want_t, true,
+                                                  per_cu ? std::atoi(per_cu) : 0);
     if (sh.rows == 0) return none;
     if (static_cast<long long>(obs_rows) * g.D * 4 > 0x7FFFFFF0LL - 0x100000LL) return none;
     for (int net = 0; net < 2; ++net)
@@ -1033,7 +1037,7 @@ FragArgs build_frags(const ppo_ctx *c, const ppo_params *p, const WsPlan &w, voi
             j.dst = base + w.frag_w[net][l];
             j.rows = g.H[l];
             j.K = K;
-            j.S = (l == 0 ? w.kpad : K) / 16;
+            j.S = (l == 0 ? w.kfrag : K) / 16;
             j.ld = K;
             j.transpose = 0;
             if (net == 1) {
@@ -1069,7 +1073,7 @@ void add_adam_frags(AdamArgs &ad, const ppo_ctx *c, const WsPlan &w, void *ws) {
             F.begin = net == 0 ? g.Wa[l] : g.Wc[l];
             F.rows = g.H[l];
             F.cols = l == 0 ? g.D : g.H[l - 1];
-            F.S = (l == 0 ? w.kpad : F.cols) / 16;
+            F.S = (l == 0 ? w.kfrag : F.cols) / 16;
             F.S_t = g.H[l] / 16;
             F.split = net == 1 ? 1 : 0;
             F.dst = base + w.frag_w[net][l];
@@ -1394,7 +1398,7 @@ int ppo_rollout_infer(const ppo_ctx *c, void *stream, const ppo_params *p, const
         }
         a.L = g.L;
         a.D = g.D;
-        a.kpad = w.kpad;
+        a.kpad = w.kfrag;
         a.A = g.A;
         for (int l = 0; l < g.L; ++l) a.H[l] = g.H[l];
         a.obs = obs;
@@ -1413,6 +1417,7 @@ int ppo_rollout_infer(const ppo_ctx *c, void *stream, const ppo_params *p, const
         a.vec_out = g.A % 4 == 0 && (!actions || aligned16(actions)) && (!mu || aligned16(mu)) ? 1 : 0;
         a.R = fsh.rows;
         a.NT = fsh.threads;
+        a.per_cu = fsh.per_cu;
         PPO_HIP(launch_fused_infer(a, s), "fused inference");
         return PPO_OK;
     }
