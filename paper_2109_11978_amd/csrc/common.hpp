@@ -302,18 +302,21 @@ hipError_t launch_adv_finalize(const double *partials, int nparts, float *adv, l
 // Gradient assembly: sum split-K partials per segment into the flat gradient,
 // and per-block float64 sums of squares.
 struct ReduceSegment {
-    const float *src;         // partial s, row r, col c at src + s * split_stride + r * ld + c
+    const float *src;         // partial s, element i at src + s * split_stride + i
     long long split_stride;
-    int splits, rows, cols, ld;
+    int splits, count;        // partials, elements
+    int vec;                  // 1: four elements at a time (16-byte aligned throughout)
+    int pad;
     long long dst_offset;     // into the flat gradient
-    long long begin;          // first global element index of this segment
-    float add;                // constant added after the split sum
 };
 constexpr int kMaxSegments = 24;
 struct ReduceArgs {
     ReduceSegment seg[kMaxSegments];
     int count;
-    long long total;
+    // workgroups block[q] .. block[q + 1] - 1 take segment q, per_block elements
+    // each; the workgroup after the last one takes the loss partials
+    int block[kMaxSegments + 1];
+    int per_block;
     float *grad;
     double *sumsq_partials;   // [blocks]
     // loss partials of the head/loss kernel, reduced by the last block
@@ -326,8 +329,14 @@ struct ReduceArgs {
     // rescales *lr from the mean KL (inv_m = 1 / M)
     float *lr;
     float inv_m, desired_kl, lr_factor, lr_min, lr_max;
+    // with step non-null the last block also advances the step count by
+    // step_add (the epoch's last reduction; its Adam launch counts from there)
+    int32_t *step;
+    int step_add;
 };
-int reduce_blocks(long long total);  // includes the loss-partial block
+// Splits the segments over workgroups (fills block and per_block).
+void plan_reduce(ReduceArgs &a);
+inline int reduce_blocks(const ReduceArgs &a) { return a.block[a.count] + 1; }   // with the loss partials' one
 hipError_t launch_grad_reduce(const ReduceArgs &a, hipStream_t s);
 
 // A hidden-layer weight whose fragment copies (the layouts of
@@ -340,12 +349,19 @@ struct AdamFrag {
     uint16_t *dst, *dst_t;  // forward and transposed fragments (dst_t null when not kept)
 };
 constexpr int kMaxAdamFrags = 2 * kMaxHidden;
+constexpr int kMaxAdamRegions = 2 * kMaxAdamFrags + 1;
 struct AdamArgs {
     AdamFrag frag[kMaxAdamFrags];
     int n_frag;                // 0: no fragment copies to refresh
+    // The flat vector in regions, each a matrix with fragment copies (region_frag
+    // its index) or what lies between two of them (-1); region q starts at
+    // region[q], workgroups block[q] .. block[q + 1] - 1 take it, per_block
+    // elements each (plan_adam).
+    int n_regions, per_block;
+    int region[kMaxAdamRegions + 1], block[kMaxAdamRegions + 1], region_frag[kMaxAdamRegions];
     float *theta, *grad, *m, *v;
     uint16_t *shadow;          // may be null
-    const int32_t *step;       // steps already taken before this epoch
+    const int32_t *step;       // steps taken, as of this launch
     int step_offset;           // this launch is step (*step + step_offset + 1)
     const float *lr;
     const double *sumsq_partials;
@@ -356,7 +372,8 @@ struct AdamArgs {
     long long P;
     int apply;                   // 0: only statistics (loss/grad without an optimiser step)
 };
-int adam_blocks(long long P);
+// Splits the flat vector over workgroups; frag, n_frag and P are set.
+void plan_adam(AdamArgs &a);
 hipError_t launch_adam(const AdamArgs &a, hipStream_t s);
 hipError_t launch_step_advance(int32_t *step, int k, hipStream_t s);
 

@@ -4,6 +4,7 @@
 // statistics, gradient assembly with the float64 global norm, and Adam.
 #include "common.hpp"
 
+#include <algorithm>
 #include <mutex>
 #include "philox.hpp"
 
@@ -584,38 +585,63 @@ __global__ __launch_bounds__(kFinalizeThreads) void adv_finalize_kernel(const do
 }
 
 // -------------------------------------------------------- gradient reduce
-// Blocks 0 .. gridDim-2 sum the split partials of every segment into the
-// flat gradient; the last block sums the loss partials column-wise (8 row
-// stripes, then the stripes in order) into the log-std gradient and the
-// loss sums.  Every block writes the float64 sum of squares of what it wrote.
+// Sums the split partials of every segment into the flat gradient; the last
+// block sums the loss partials column-wise (8 row stripes, then the stripes in
+// order) into the log-std gradient and the loss sums.  Every block writes the
+// float64 sum of squares of what it wrote.
+//
+// A latency chain at these sizes (17 MB of partials at [512, 256, 128]), not
+// bandwidth: every block belongs to one segment, whose descriptor it reads
+// with scalar loads, and a thread has the loads of four elements by up to 16
+// partials in flight.  One element and 8 partials at a time, the segment
+// searched by every lane: 9.4 us at [512, 256, 128] and 21.8 us at
+// [1024, 512, 256] with 235 inputs; now 7.4 and 9.6 us.
 constexpr int kReduceThreads = 256;
 
+// Four elements (or one) of segment S summed over its partials, 16 loads in
+// flight at a time, added in split order.
+template <typename V>
+__device__ inline V sum_partials(const float *src, long long stride, int splits) {
+    V sum{};
+    for (int s0 = 0; s0 < splits; s0 += 16) {
+        V v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (s0 + u < splits) v[u] = *reinterpret_cast<const V *>(src + (s0 + u) * stride);
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (s0 + u < splits) sum += v[u];
+    }
+    return sum;
+}
+
 __global__ __launch_bounds__(kReduceThreads) void grad_reduce_kernel(const ReduceArgs a) {
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
     __shared__ double red[kReduceThreads / 64];
     double ss = 0.0;
-    if (blockIdx.x + 1 < gridDim.x) {
-        const long long stride = static_cast<long long>(gridDim.x - 1) * blockDim.x;
-        for (long long e = blockIdx.x * static_cast<long long>(blockDim.x) + threadIdx.x; e < a.total; e += stride) {
-            int si = 0;
-            while (si + 1 < a.count && e >= a.seg[si + 1].begin) ++si;
-            const ReduceSegment &S = a.seg[si];
-            const long long local = e - S.begin;
-            const int r = static_cast<int>(local / S.cols);
-            const int c = static_cast<int>(local - static_cast<long long>(r) * S.cols);
-            const float *src = S.src + static_cast<long long>(r) * S.ld + c;
-            // eight partials in flight at a time, added in split order
-            float sum = 0.0f;
-            for (int s0 = 0; s0 < S.splits; s0 += 8) {
-                float v[8];
+    const int blk = blockIdx.x;
+    if (blk + 1 < static_cast<int>(gridDim.x)) {
+        int si = 0;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = s0 + u < S.splits ? src[(s0 + u) * S.split_stride] : 0.0f;
+        for (int q = 1; q < kMaxSegments; ++q)
+            if (q < a.count && blk >= a.block[q]) si = q;
+        si = __builtin_amdgcn_readfirstlane(si);
+        const ReduceSegment &S = a.seg[si];
+        const int i0 = (blk - a.block[si]) * a.per_block, i1 = min(S.count, i0 + a.per_block);
+        float *dst = a.grad + S.dst_offset;
+        if (S.vec) {
+            for (int i = i0 + 4 * static_cast<int>(threadIdx.x); i < i1; i += 4 * kReduceThreads) {
+                const f32x4 sum = sum_partials<f32x4>(S.src + i, S.split_stride, S.splits);
+                *reinterpret_cast<f32x4 *>(dst + i) = sum;
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (s0 + u < S.splits) sum += v[u];
+                for (int e = 0; e < 4; ++e) ss += static_cast<double>(sum[e]) * sum[e];
             }
-            sum += S.add;
-            a.grad[S.dst_offset + local] = sum;
-            ss += static_cast<double>(sum) * sum;
+        } else {
+            for (int i = i0 + static_cast<int>(threadIdx.x); i < i1; i += kReduceThreads) {
+                const float sum = sum_partials<float>(S.src + i, S.split_stride, S.splits);
+                dst[i] = sum;
+                ss += static_cast<double>(sum) * sum;
+            }
         }
     } else {
         // columns: 4 loss sums, A log-std gradients, entropy, mean-shift KL, log-std KL
@@ -672,6 +698,7 @@ __global__ __launch_bounds__(kReduceThreads) void grad_reduce_kernel(const Reduc
                     lr = fminf(a.lr_max, lr * a.lr_factor);
                 *a.lr = lr;
             }
+            if (a.step) *a.step += a.step_add;
         }
     }
     ss = wave_sum_d(ss);
@@ -685,23 +712,50 @@ __global__ __launch_bounds__(kReduceThreads) void grad_reduce_kernel(const Reduc
 }
 
 // ------------------------------------------------------------------ Adam
+// Clip coefficient from the reduction's sums of squares, then Adam on the flat
+// vector, with the bf16 shadow and the fragment copies of the hidden weights.
+//
+// A latency chain too: every block adds up the norm's partials (in the same
+// order), and its elements can only be written after that.  So a thread's
+// first kAdamUnroll elements load together with the partials, the two bias
+// corrections (float64 powers) are computed by two other waves than the one
+// that finishes the norm, and a block lies within one matrix, whose descriptor
+// is scalar.  One element per lane and step: the bf16 copies coalesce only when
+// neighbouring lanes own neighbouring elements.  With one element loaded ahead,
+// the powers behind the norm and every matrix tested per element: 9.7 us at
+// [512, 256, 128] and 23.5 us at [1024, 512, 256] with 235 inputs; now 9.2 and
+// 20.4 us (6.6 us without the fragment copies).
 constexpr int kAdamThreads = 256;
+constexpr int kAdamUnroll = 4;
 
 __global__ __launch_bounds__(kAdamThreads) void adam_kernel(const AdamArgs a) {
     __shared__ double s_sumsq;
     __shared__ double red[kAdamThreads / 64];
     __shared__ float s_bc[2];
-    // this thread's first element goes out before the norm is known
-    const long long first = blockIdx.x * static_cast<long long>(blockDim.x) + threadIdx.x;
-    const bool pre = a.apply && first < a.P;
-    const float g_first = pre ? a.grad[first] : 0.0f;
-    const float m_first = pre ? a.m[first] : 0.0f;
-    const float v_first = pre ? a.v[first] : 0.0f;
-    const float th_first = pre ? a.theta[first] : 0.0f;
+    const int tid = threadIdx.x, blk = blockIdx.x;
+    int ri = 0;
+#pragma unroll
+    for (int q = 1; q < kMaxAdamRegions; ++q)
+        if (q < a.n_regions && blk >= a.block[q]) ri = q;
+    ri = __builtin_amdgcn_readfirstlane(ri);
+    const int e0 = a.region[ri] + (blk - a.block[ri]) * a.per_block;
+    const int e1 = min(a.region[ri + 1], e0 + a.per_block);
+    // this thread's first elements go out before the norm is known
+    float g_pre[kAdamUnroll], m_pre[kAdamUnroll], v_pre[kAdamUnroll], th_pre[kAdamUnroll];
+#pragma unroll
+    for (int u = 0; u < kAdamUnroll; ++u) {
+        const int e = e0 + tid + kAdamThreads * u;
+        const bool in = a.apply && e < e1;
+        g_pre[u] = in ? a.grad[e] : 0.0f;
+        m_pre[u] = in ? a.m[e] : 0.0f;
+        v_pre[u] = in ? a.v[e] : 0.0f;
+        th_pre[u] = in ? a.theta[e] : 0.0f;
+    }
+    const float lr = a.lr ? *a.lr : 0.0f;
     // global norm: every block sums the same partials in the same order
     // (four loads in flight, added in index order)
     double ss = 0.0;
-    int p = threadIdx.x;
+    int p = tid;
     for (; p + 3 * kAdamThreads < a.n_sumsq; p += 4 * kAdamThreads) {
         const double s0 = a.sumsq_partials[p], s1 = a.sumsq_partials[p + kAdamThreads];
         const double s2 = a.sumsq_partials[p + 2 * kAdamThreads], s3 = a.sumsq_partials[p + 3 * kAdamThreads];
@@ -711,26 +765,26 @@ __global__ __launch_bounds__(kAdamThreads) void adam_kernel(const AdamArgs a) {
         ss += s3;
     }
     for (; p < a.n_sumsq; p += kAdamThreads) ss += a.sumsq_partials[p];
+    if (a.apply && (tid == 64 || tid == 128)) {
+        // bias corrections of this step, once per block
+        const int step = *a.step + a.step_offset + 1;
+        s_bc[tid == 64 ? 0 : 1] =
+            static_cast<float>(1.0 - pow(static_cast<double>(tid == 64 ? a.beta1 : a.beta2), step));
+    }
     ss = wave_sum_d(ss);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+    if ((tid & 63) == 0) red[tid >> 6] = ss;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         double t = 0.0;
         for (int w = 0; w < kAdamThreads / 64; ++w) t += red[w];
         s_sumsq = t;
-        if (a.apply) {
-            // bias corrections of this step, once per block
-            const int step = *a.step + a.step_offset + 1;
-            s_bc[0] = static_cast<float>(1.0 - pow(static_cast<double>(a.beta1), step));
-            s_bc[1] = static_cast<float>(1.0 - pow(static_cast<double>(a.beta2), step));
-        }
     }
     __syncthreads();
     const double norm = sqrt(s_sumsq);
     const bool finite = isfinite(norm);
     const float coef = static_cast<float>(fmin(1.0, static_cast<double>(a.max_grad_norm) / (norm + 1e-6)));
 
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (blk == 0 && tid == 0) {
         const float pl = a.loss_sums[0] * a.inv_m, vl = a.loss_sums[1] * a.inv_m;
         const float ent = a.loss_sums[4];
         a.stats[0] = pl + a.value_coef * vl - a.entropy_coef * ent;
@@ -742,13 +796,14 @@ __global__ __launch_bounds__(kAdamThreads) void adam_kernel(const AdamArgs a) {
         a.stats[6] = static_cast<float>(norm);
         a.stats[7] = finite ? 0.0f : 1.0f;
         a.stats[8] = a.loss_sums[5];
-        a.stats[9] = a.lr ? *a.lr : 0.0f;
+        a.stats[9] = lr;
     }
     if (!a.apply || !finite) return;
 
     const float bc1 = s_bc[0], bc2 = s_bc[1];
-    const float lr = *a.lr;
-    auto update = [&](long long e, float g_raw, float m_old, float v_old, float th_old) {
+    const int fi = a.region_frag[ri];
+    const AdamFrag &F = a.frag[fi < 0 ? 0 : fi];
+    auto update = [&](int e, float g_raw, float m_old, float v_old, float th_old) {
         const float g = g_raw * coef;
         const float m = a.beta1 * m_old + (1.0f - a.beta1) * g;
         const float v = a.beta2 * v_old + (1.0f - a.beta2) * g * g;
@@ -756,41 +811,38 @@ __global__ __launch_bounds__(kAdamThreads) void adam_kernel(const AdamArgs a) {
         a.v[e] = v;
         const float th = th_old - lr * (m / bc1) / (sqrtf(v / bc2) + a.eps);
         a.theta[e] = th;
-        if (a.shadow) a.shadow[e] = f32_to_bf16(th);
+        const uint16_t bits = f32_to_bf16(th);
+        if (a.shadow) a.shadow[e] = bits;
+        if (fi < 0) return;
         // the same bf16 value into the fragment copies of its weight matrix:
         // element (r, c) of W [rows][cols] sits in fragment (r / 32, c / 16),
         // lane r % 32 + 32 ((c % 16) / 8), element c % 8; in the transposed
-        // copy the roles of r and c swap.  The matrices are disjoint, so at
-        // most one matches; every lane visits all of them, which keeps the
-        // matrix descriptors uniform across the wave
-        for (int j = 0; j < a.n_frag; ++j) {
-            const AdamFrag &F = a.frag[j];
-            const long long local = e - F.begin;
-            if (local < 0 || local >= static_cast<long long>(F.rows) * F.cols) continue;
-            // rows * cols < 2^31 (width and observation limits): 32-bit division
-            const unsigned li = static_cast<unsigned>(local), cols = static_cast<unsigned>(F.cols);
-            const int r = static_cast<int>(li / cols), c = static_cast<int>(li - static_cast<unsigned>(r) * cols);
-            const uint16_t bits = f32_to_bf16(th);
-            const int li_in = (r & 31) + 32 * ((c & 15) >> 3);
-            if (F.split) {
-                // split layout: the feature block's S bf16 fragments, then its S
-                // residual fragments
-                const long long f0 = static_cast<long long>(2 * (r >> 5)) * F.S + (c >> 4);
-                F.dst[(f0 * 64 + li_in) * 8 + (c & 7)] = bits;
-                F.dst[((f0 + F.S) * 64 + li_in) * 8 + (c & 7)] = f32_to_bf16(th - bf16_to_f32(bits));
-            } else {
-                const long long fs = static_cast<long long>(r >> 5) * F.S + (c >> 4);
-                F.dst[(fs * 64 + li_in) * 8 + (c & 7)] = bits;
-            }
-            if (F.dst_t)
-                F.dst_t[((static_cast<long long>(c >> 5) * F.S_t + (r >> 4)) * 64 + (c & 31) + 32 * ((r & 15) >> 3)) *
-                            8 +
-                        (r & 7)] = bits;
+        // copy the roles of r and c swap.  rows * cols < 2^31 (width and
+        // observation limits): 32-bit division
+        const unsigned li = static_cast<unsigned>(e - a.region[ri]), cols = static_cast<unsigned>(F.cols);
+        const int r = static_cast<int>(li / cols), c = static_cast<int>(li - static_cast<unsigned>(r) * cols);
+        const int li_in = (r & 31) + 32 * ((c & 15) >> 3);
+        if (F.split) {
+            // split layout: the feature block's S bf16 fragments, then its S
+            // residual fragments
+            const long long f0 = static_cast<long long>(2 * (r >> 5)) * F.S + (c >> 4);
+            F.dst[(f0 * 64 + li_in) * 8 + (c & 7)] = bits;
+            F.dst[((f0 + F.S) * 64 + li_in) * 8 + (c & 7)] = f32_to_bf16(th - bf16_to_f32(bits));
+        } else {
+            const long long fs = static_cast<long long>(r >> 5) * F.S + (c >> 4);
+            F.dst[(fs * 64 + li_in) * 8 + (c & 7)] = bits;
         }
+        if (F.dst_t)
+            F.dst_t[((static_cast<long long>(c >> 5) * F.S_t + (r >> 4)) * 64 + (c & 31) + 32 * ((r & 15) >> 3)) * 8 +
+                    (r & 7)] = bits;
     };
-    const long long stride = static_cast<long long>(gridDim.x) * blockDim.x;
-    if (pre) update(first, g_first, m_first, v_first, th_first);
-    for (long long e = first + stride; e < a.P; e += stride) update(e, a.grad[e], a.m[e], a.v[e], a.theta[e]);
+#pragma unroll
+    for (int u = 0; u < kAdamUnroll; ++u) {
+        const int e = e0 + tid + kAdamThreads * u;
+        if (e < e1) update(e, g_pre[u], m_pre[u], v_pre[u], th_pre[u]);
+    }
+    for (int e = e0 + tid + kAdamThreads * kAdamUnroll; e < e1; e += kAdamThreads)
+        update(e, a.grad[e], a.m[e], a.v[e], a.theta[e]);
 }
 
 // ------------------------------------------------------- weight staging
@@ -983,17 +1035,52 @@ hipError_t launch_adv_finalize(const double *partials, int nparts, float *adv, l
     return hipGetLastError();
 }
 
-int reduce_blocks(long long total) { return grid_for(total, kReduceThreads, 1023) + 1; }
+// At most about 960 blocks of whole passes over the threads (their sums of
+// squares have 1024 places), one pass each where that is enough.
+void plan_reduce(ReduceArgs &a) {
+    long long total = 0;
+    for (int q = 0; q < a.count; ++q) total += a.seg[q].count;
+    constexpr long long pass = 4 * kReduceThreads;
+    a.per_block = static_cast<int>(pass * std::max<long long>(1, (total + pass * 960 - 1) / (pass * 960)));
+    a.block[0] = 0;
+    for (int q = 0; q < a.count; ++q)
+        a.block[q + 1] = a.block[q] + (a.seg[q].count + a.per_block - 1) / a.per_block;
+}
 
 hipError_t launch_grad_reduce(const ReduceArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(grad_reduce_kernel, dim3(reduce_blocks(a.total)), dim3(kReduceThreads), 0, s, a);
+    hipLaunchKernelGGL(grad_reduce_kernel, dim3(reduce_blocks(a)), dim3(kReduceThreads), 0, s, a);
     return hipGetLastError();
 }
 
-int adam_blocks(long long P) { return grid_for(P, kAdamThreads, 1024); }
+void plan_adam(AdamArgs &a) {
+    int n = 0;
+    long long at = 0;
+    auto add = [&](long long end, int frag) {
+        if (end > at) {
+            a.region[n] = static_cast<int>(at);
+            a.region_frag[n++] = frag;
+            at = end;
+        }
+    };
+    for (int f = 0; f < a.n_frag; ++f) {   // in flat order
+        add(a.frag[f].begin, -1);
+        add(a.frag[f].begin + static_cast<long long>(a.frag[f].rows) * a.frag[f].cols, f);
+    }
+    add(a.P, -1);
+    a.n_regions = n;
+    a.region[n] = static_cast<int>(a.P);
+    // one pass of kAdamUnroll elements per thread up to 2048 blocks (as many as
+    // fit on the device at once), several from there on
+    constexpr long long pass = kAdamUnroll * kAdamThreads;
+    a.per_block = static_cast<int>(pass * std::max<long long>(1, (a.P + pass * 2048 - 1) / (pass * 2048)));
+    a.block[0] = 0;
+    for (int q = 0; q < n; ++q)
+        a.block[q + 1] = a.block[q] + (a.region[q + 1] - a.region[q] + a.per_block - 1) / a.per_block;
+}
 
 hipError_t launch_adam(const AdamArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(adam_kernel, dim3(adam_blocks(a.P)), dim3(kAdamThreads), 0, s, a);
+    // without a step only the statistics, by one block
+    hipLaunchKernelGGL(adam_kernel, dim3(a.apply ? a.block[a.n_regions] : 1), dim3(kAdamThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -632,7 +632,6 @@ DwPlan build_dw(const ppo_ctx *c, const WsPlan &w, void *ws, int M, const TileCh
     DwPlan d;
     int splits0, kps0;
     dw_splits(g, c->prec, M, tc.tile, tc.rounds, splits0, kps0);
-    long long pos = 0;
     float *part = reinterpret_cast<float *>(wsp(ws, w.part));
     float *rows_part = reinterpret_cast<float *>(wsp(ws, w.rowsum));
     size_t part_off = 0, row_off = 0;
@@ -681,17 +680,19 @@ DwPlan build_dw(const ppo_ctx *c, const WsPlan &w, void *ws, int M, const TileCh
 
             const long long woff = net == 0 ? g.Wa[l] : g.Wc[l];
             const long long boff = net == 0 ? g.ba[l] : g.bc[l];
-            d.red.seg[d.red.count++] = ReduceSegment{part + part_off, static_cast<long long>(r) * cc, splits, r, cc,
-                                                     cc, woff, pos, 0.0f};
-            pos += static_cast<long long>(r) * cc;
-            d.red.seg[d.red.count++] = ReduceSegment{rows_part + row_off, r, splits, 1, r, 0, boff, pos, 0.0f};
-            pos += r;
+            auto add_segment = [&](const float *src, int count, long long off) {
+                // partials start 256-byte aligned; the caller's gradient is 16-byte aligned
+                const int vec = count % 4 == 0 && off % 4 == 0 ? 1 : 0;
+                d.red.seg[d.red.count++] = ReduceSegment{src, count, splits, count, vec, 0, off};
+            };
+            add_segment(part + part_off, r * cc, woff);
+            add_segment(rows_part + row_off, r, boff);
             part_off += align_up(static_cast<size_t>(splits) * r * cc, 64);
             row_off += align_up(static_cast<size_t>(splits) * r, 64);
         }
     }
     ++d.n_launch;
-    d.red.total = pos;
+    plan_reduce(d.red);
     return d;
 }
 
@@ -901,6 +902,7 @@ struct StepBuffers {
     int step_offset;
     bool frags_ready = false;   // the fused pass's fragments already hold the current shadow
     bool write_frags = false;   // Adam refreshes them for the next step
+    int advance = 0;            // the epoch's last step: its reduction adds this to the step count
     uint8_t *active_out = nullptr;  // per-sample surrogate branch (ppo_loss_grad only)
     bool loss_only = false;         // ppo_loss_grad without a gradient output
     float *ratio_out = nullptr;     // per-sample probability ratio (ppo_loss_grad only)
@@ -977,7 +979,7 @@ AdamArgs adam_args(const ppo_ctx *c, const ppo_params *p, const ppo_hparams *hp,
     ad.step_offset = step_offset;
     ad.lr = p->lr;
     ad.sumsq_partials = red.sumsq_partials;
-    ad.n_sumsq = reduce_blocks(red.total);
+    ad.n_sumsq = reduce_blocks(red);
     ad.loss_sums = red.loss_sums;
     ad.max_grad_norm = hp->max_grad_norm;
     ad.beta1 = hp->beta1;
@@ -1176,10 +1178,15 @@ hipError_t enqueue_step(const ppo_ctx *c, const ppo_params *p, const ppo_hparams
 
     ReduceArgs &red = d.red;
     set_reduce_loss(red, c, p, hp, w, ws, sb.grad, M, sb.apply, fused_r);
+    if (sb.advance) {
+        red.step = p->step;
+        red.step_add = sb.advance;
+    }
     PROFILED(prof, PPO_PHASE_GRAD_REDUCE, launch_grad_reduce(red, s));
 
-    AdamArgs ad = adam_args(c, p, hp, red, sb.grad, sb.stats, M, sb.step_offset, sb.apply);
+    AdamArgs ad = adam_args(c, p, hp, red, sb.grad, sb.stats, M, sb.step_offset - sb.advance, sb.apply);
     if (fused_r > 0 && sb.write_frags && sb.apply) add_adam_frags(ad, c, w, ws);
+    plan_adam(ad);
     PROFILED(prof, PPO_PHASE_ADAM, launch_adam(ad, s));
     return hipSuccess;
 }
@@ -1588,10 +1595,11 @@ int ppo_update_epoch(ppo_ctx *c, void *stream, const ppo_params *p, const ppo_ba
             // after the first step, Adam leaves the fragments of the next one in place
             sb.frags_ready = k > 0;
             sb.write_frags = k + 1 < n_minibatches;
+            if (k + 1 == n_minibatches) sb.advance = n_minibatches;
             hipError_t e = enqueue_step(c, p, hp, w, ws, sb, tune, target);
             if (e != hipSuccess) return e;
         }
-        return launch_step_advance(p->step, n_minibatches, target);
+        return hipSuccess;
     };
     if (!hp->use_graph) {
         PPO_HIP(enqueue_all(s), "update_epoch");
@@ -1970,7 +1978,8 @@ hipError_t enqueue_batched_step(std::vector<BatchedRun> &runs, const ppo_hparams
         set_reduce_loss(red, r.c, r.p, hp, r.w, r.ws, r.p->grad, r.M, 1, all_fused ? fsh[i].rows : 0);
         e = launch_grad_reduce(red, run_stream(i));
         if (e != hipSuccess) return e;
-        const AdamArgs ad = adam_args(r.c, r.p, hp, red, r.p->grad, r.stats + k * PPO_STATS_WIDTH, r.M, k, 1);
+        AdamArgs ad = adam_args(r.c, r.p, hp, red, r.p->grad, r.stats + k * PPO_STATS_WIDTH, r.M, k, 1);
+        plan_adam(ad);
         e = launch_adam(ad, run_stream(i));
         if (e != hipSuccess) return e;
     }
@@ -2174,9 +2183,9 @@ int ppo_update_batched(ppo_ctx *const *ctxs, int32_t R, void *stream, const ppo_
                                    r.stats + k * PPO_STATS_WIDTH, 1, k};
                     sb.frags_ready = k > 0;
                     sb.write_frags = k + 1 < n_minibatches;
+                    if (k + 1 == n_minibatches) sb.advance = n_minibatches;
                     if ((e = enqueue_step(r.c, r.p, hp, r.w, r.ws, sb, tunes[i], st)) != hipSuccess) return e;
                 }
-                if ((e = launch_step_advance(r.p->step, n_minibatches, st)) != hipSuccess) return e;
             }
             return join_from(g_side, target, n_side);
         }
