@@ -262,7 +262,7 @@ int ppo_gae(const ppo_ctx *ctx, void *stream, const float *rewards, const uint8_
  * device memory (code under HIP graph capture, serving loops, harnesses that
  * forbid allocation): the same computation and results bit for bit, with no
  * workspace argument.  The per-block statistics partials it needs (24 bytes
- * per 256 environments) live in a fixed device array of the library, one per
+ * each, at most one per 64 environments) live in a fixed device array of the library, one per
  * GPU, held until the process ends; N must not exceed PPO_GAE_NOALLOC_MAX_N
  * (PPO_E_SHAPE otherwise, before anything is enqueued).  The first call on a
  * device looks up that device's copy of the array (with the device current)

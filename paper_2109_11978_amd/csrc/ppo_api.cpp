@@ -245,7 +245,7 @@ WsPlan plan_workspace(const NetLayout &g, Precision prec, int N, int T, int M) {
     w.loss_part = a.take(static_cast<size_t>(head_loss_blocks(mm)) * head_loss_partial_width(g.A) * 4);
     w.loss_sums = a.take(8 * 4);
     w.sumsq = a.take(static_cast<size_t>(1024) * 8);
-    w.gae_part = a.take(static_cast<size_t>(gae_blocks(std::max(N, 1))) * 3 * 8);
+    w.gae_part = a.take(static_cast<size_t>(gae_max_blocks(std::max(N, 1))) * 3 * 8);
     w.pad_w0 = g.D != w.kpad;
     size_t wt_elems = 0;
     for (int net = 0; net < 2; ++net) {
