@@ -202,6 +202,7 @@ void dw_splits(const NetLayout &g, Precision prec, int M, int tile, int rounds, 
 // Largest split count any tuning candidate may use (sizes the partials).
 int dw_max_splits(const NetLayout &g, Precision prec, int M) {
     int best = 1;
+    if (M < 4 * gemm_bk(prec)) return best;   // one split holds at least two k-slabs
     for (int t = 0; t < kNumTileShapes; ++t)
         for (int rounds : {1, 2, 4}) {
             int sp, kps;
