@@ -33,12 +33,14 @@ __host__ __device__ inline uint16_t f32_to_bf16(float f) {
 }
 
 // Log-density of a diagonal Gaussian in float32 with compensated summation.
-// s carries the sum, c the rounding errors of its additions (Neumaier's
-// variant of Kahan summation) plus the exact errors of the squares (from a
-// fused multiply-add) and the float32 residual of ln(2 pi) / 2, so the
+// s carries the sum, c the rounding errors of its additions (Knuth's two-sum:
+// exact whichever operand is larger) plus the exact errors of the squares
+// (from a fused multiply-add) and the float32 residual of ln(2 pi) / 2, so the
 // result is within a few float32 ulps of the exact sum of the float32
 // inputs.  Contraction is off: each product and sum is rounded on its own,
-// as the error terms assume.
+// as the error terms assume.  Straight-line code: the sums are one dependent
+// chain, which the compiler fills with the error terms of other dimensions
+// only where no branch lies between them.
 constexpr float kHalfLog2PiHi = 0.918938517570495605f;
 constexpr float kHalfLog2PiLo = static_cast<float>(0.91893853320467274178 - static_cast<double>(kHalfLog2PiHi));
 struct CompSum {
@@ -46,18 +48,20 @@ struct CompSum {
     __device__ inline void add(float x) {
 #pragma clang fp contract(off)
         const float t = s + x;
-        c += fabsf(s) >= fabsf(x) ? (s - t) + x : (x - t) + s;
+        const float b = t - s;
+        c += (s - (t - b)) + (x - b);
         s = t;
     }
-    // one dimension of a diagonal-Gaussian log-density: -z^2 / 2 - log sigma - ln(2 pi) / 2
-    __device__ inline void add_gauss(float z, float logstd) {
+    // one dimension of a diagonal-Gaussian log-density: -z^2 / 2 - log sigma -
+    // ln(2 pi) / 2; nothing (zeros, which leave s and c as they are) when !on
+    __device__ inline void add_gauss(float z, float logstd, bool on = true) {
 #pragma clang fp contract(off)
         const float p = z * z;
         const float e = __builtin_fmaf(z, z, -p);   // p + e = z^2 exactly
-        add(-0.5f * p);
-        add(-logstd);
-        add(-kHalfLog2PiHi);
-        c += -0.5f * e - kHalfLog2PiLo;
+        add(on ? -0.5f * p : 0.0f);
+        add(on ? -logstd : 0.0f);
+        add(on ? -kHalfLog2PiHi : 0.0f);
+        c += on ? -0.5f * e - kHalfLog2PiLo : 0.0f;
     }
     __device__ inline float value() const { return s + c; }
 };

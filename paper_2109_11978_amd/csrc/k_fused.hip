@@ -416,9 +416,17 @@ __device__ inline void copy_out(const uint16_t *src, int pitch, uint16_t *dst, i
 // takes rows w, w + NW, ...; its lanes take consecutive 16-byte chunks of
 // those rows (coalesced), four loads in flight per lane (out-of-range ones
 // read zero).
-template <int R, int NT>
+template <int R, int NT, class Hook = NoHook>
 __device__ inline void gather_rows(const FusedArgs &a, const int *s_rows, int rows, uint16_t *x, int pitch,
-                                   int wave, int lane, int m0 = 0) {
+                                   int wave, int lane, int m0 = 0, const Hook &hook = Hook()) {
+    // work that fits in the first loads' latency
+    auto meanwhile = [&](int t0) {
+        if constexpr (!std::is_same<Hook, NoHook>::value) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (t0 == 0) hook();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
     constexpr int NW = NT / 64;
     constexpr int PER_WAVE = R / NW;
     const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.obs, static_cast<long long>(a.B) * a.D * 4);
@@ -442,6 +450,7 @@ __device__ inline void gather_rows(const FusedArgs &a, const int *s_rows, int ro
                 v[u] = make_float4(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]),
                                    __uint_as_float(w[3]));
             }
+            meanwhile(t0);
 #pragma unroll
             for (int u = 0; u < V; ++u) {
                 const int t = t0 + 64 * u + lane;
@@ -480,6 +489,7 @@ __device__ inline void gather_rows(const FusedArgs &a, const int *s_rows, int ro
             const bool ok = t0 + 64 * u + lane < total && i < rows;
             w[u] = __builtin_amdgcn_raw_buffer_load_b128(ru, ok ? ((e0[u] >> 2) + c) * 16 : kOutside, 0, 0);
         }
+        meanwhile(t0);
 #pragma unroll
         for (int u = 0; u < V; ++u) {
             const int t = t0 + 64 * u + lane;
@@ -795,7 +805,7 @@ __device__ __forceinline__ void head_mfma(const FusedArgs &a, const FusedNet &N,
                 const float ls = s_head[kFusedMaxAct + j];
                 inv_sig[t] = expf(-ls);
                 z[t] = (in_s[j] - o[t]) * inv_sig[t];
-                if (j < A) lr.add_gauss(z[t], ls);
+                lr.add_gauss(z[t], ls, j < A);
                 // mean-shift part of KL(pi_old || pi), only with collection-time means
                 const float dm = (in_s[kFusedMaxAct + j] - o[t]) * inv_sig[t];
                 if (a.mu_old && j < A) kl_mu += 0.5f * dm * dm;
@@ -1313,13 +1323,59 @@ constexpr int kNarrowRows = 32, kNarrowThreads = 128;
 // per_cu of the wide pass's shape (wide_infer_kernel)
 constexpr int kWidePass = -1;
 
+// The actor's noise: lane kq of an environment's KP draws action group kq (KP >=
+// 4, at most 4 groups) with Philox counter (n groups + kq, t, iteration, 1) and
+// two Box-Muller pairs, and loads the sigmas of its four actions; the
+// environment's first lane sums the log-density over the actions in order and
+// writes it.  Needs no network output, so it runs while the observations load.
+// In the head, after the means, it was 8K of the 34K cycles of an actor's block
+// (4.7K of them the log-density's chain of additions); 24 steps of 4096
+// environments with D = 48 and [128, 64, 32] took 427 us so and take 413.
+struct ActorNoise {
+    float eps[4], sig[4];
+};
+template <int KP>
+__device__ __forceinline__ ActorNoise actor_noise(const FusedArgs &a, int m0, int rows) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int A = a.A;
+    const int si = tid / KP, kq = tid % KP;
+    const int n = m0 + si;
+    const int groups = (A + 3) / 4;
+    ActorNoise z;
+    float ls[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ls[q] = a.logstd[min(4 * kq + q, A - 1)];
+    uint32_t c[4] = {static_cast<uint32_t>(n) * groups + kq, a.t_step, a.iteration, 1u};
+    philox4x32_10(c, a.key0, a.key1);
+    box_muller(c[0], c[1], z.eps[0], z.eps[1]);
+    box_muller(c[2], c[3], z.eps[2], z.eps[3]);
+    if (a.logp_out) {
+        auto density = [&](auto dims) {
+            constexpr int NO = decltype(dims)::value;
+            CompSum lp;
+#pragma unroll
+            for (int j = 0; j < NO; ++j) {
+                const float e = j < 4 ? z.eps[j % 4] : __shfl(z.eps[j % 4], lane + j / 4);
+                lp.add_gauss(e, a.logstd[min(j, A - 1)], j < A);
+            }
+            return lp.value();
+        };
+        const float lp = A <= 12 ? density(std::integral_constant<int, 12>())
+                                 : density(std::integral_constant<int, kFusedMaxAct>());
+        if (kq == 0 && si < rows) a.logp_out[n] = lp;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) z.sig[q] = expf(ls[q]);
+    return z;
+}
+
 // Output layer of the block's environments (last hidden layer hl, rows of
-// Hl + 8), then the actor's draw and its log-density or the critic's value.
-// KP adjacent lanes per environment.
+// Hl + 8), then the actor's means and actions or the critic's value.  KP
+// adjacent lanes per environment.
 template <int KP>
 __device__ __forceinline__ void infer_head(const FusedArgs &a, int net, const uint16_t *hl, const float *w_out,
-                                           const float *s_head, int m0, int rows) {
-    const int tid = threadIdx.x, lane = tid & 63;
+                                           const float *s_head, const ActorNoise &z, int m0, int rows) {
+    const int tid = threadIdx.x;
     const int A = a.A;
     const int Hl = a.H[a.L - 1];
     const int WP = Hl + 4;
@@ -1353,26 +1409,17 @@ __device__ __forceinline__ void infer_head(const FusedArgs &a, int net, const ui
         else if (nck == 4) { u32x4 hx[4]; head_dots<KP, 4, kFusedMaxAct>(hrow, wl, WP, s_head, hx, o); }
         else { u32x4 hx[8]; head_dots<KP, 8, kFusedMaxAct>(hrow, wl, WP, s_head, hx, o); }
     }
-    // lane kq of a sample draws action group kq (KP >= 4 lanes per sample,
-    // at most 4 groups); every lane holds all the sample's means
+    // every lane holds all the environment's means; lane kq writes its group
     const int groups = (A + 3) / 4;
     const bool draws = si < rows && kq < groups;
-    float eps[4];
-    {
-        uint32_t c[4] = {static_cast<uint32_t>(n) * groups + kq, a.t_step, a.iteration, 1u};
-        philox4x32_10(c, a.key0, a.key1);
-        box_muller(c[0], c[1], eps[0], eps[1]);
-        box_muller(c[2], c[3], eps[2], eps[3]);
-    }
     float act4[4], mu4[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         float m = o[q];
 #pragma unroll
         for (int g = 1; g < kFusedMaxAct / 4; ++g) m = kq == g ? o[4 * g + q] : m;
-        const int j = 4 * kq + q;
         mu4[q] = m;
-        act4[q] = m + expf(s_head[kFusedMaxAct + min(j, kFusedMaxAct - 1)]) * eps[q];
+        act4[q] = m + z.sig[q] * z.eps[q];
     }
     if (a.vec_out) {
         // the lane's group of four actions and means, one 16-byte store each
@@ -1391,18 +1438,6 @@ __device__ __forceinline__ void infer_head(const FusedArgs &a, int net, const ui
             }
         }
     }
-    // the lead lane sums the log-density over the actions in order
-    float e_all[kFusedMaxAct];
-#pragma unroll
-    for (int g = 0; g < kFusedMaxAct / 4; ++g)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) e_all[4 * g + q] = g == 0 ? eps[q] : __shfl(eps[q], lane + g);
-    if (!lead || !a.logp_out) return;
-    CompSum lp;
-#pragma unroll
-    for (int j = 0; j < kFusedMaxAct; ++j)
-        if (j < A) lp.add_gauss(e_all[j], s_head[kFusedMaxAct + j]);
-    a.logp_out[n] = lp.value();
 }
 
 // Rollout inference for R environments of one network per workgroup: the
@@ -1437,6 +1472,7 @@ void fused_infer_kernel(const FusedArgs a) {
     const FusedNet &N = a.net[net];
     uint16_t *x = reinterpret_cast<uint16_t *>(lds + a.lds_x);
     const int xp = a.kpad + 8;
+    ActorNoise noise{};
     {
         // output-layer weights, output biases, log-std and hidden biases in one
         // round of buffer loads, then the LDS stores (as in the update pass)
@@ -1463,7 +1499,9 @@ void fused_infer_kernel(const FusedArgs a) {
         const float vl = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rl, tid < A ? tid * 4 : kOutside, 0, 0));
         // the observation rows are the block's own (no index list): their loads
         // go out behind the weight loads, so the prologue waits for memory once
-        gather_rows<R, NT>(a, nullptr, rows, x, xp, wave, lane, m0);
+        gather_rows<R, NT>(a, nullptr, rows, x, xp, wave, lane, m0, [&]() {
+            if (net == 0) noise = actor_noise<KP>(a, m0, rows);
+        });
 #pragma unroll
         for (int u = 0; u < UW; ++u) {
             const int q = 4 * (tid + u * NT);
@@ -1505,7 +1543,8 @@ void fused_infer_kernel(const FusedArgs a) {
         K = H;
     }
 
-    infer_head<KP>(a, net, reinterpret_cast<const uint16_t *>(lds + a.lds_region[L - 1]), w_out, s_head, m0, rows);
+    infer_head<KP>(a, net, reinterpret_cast<const uint16_t *>(lds + a.lds_region[L - 1]), w_out, s_head, noise, m0,
+                   rows);
 }
 
 // Rollout inference for networks whose first hidden layer is too wide for
@@ -1525,7 +1564,7 @@ void fused_infer_kernel(const FusedArgs a) {
 // each later layer writes over its input.  The critic's blocks, the longer
 // ones, come first in the grid, so the second round of workgroups is the
 // shorter one.  One call over 16384 environments of [1024, 512, 256] with 235
-// inputs: layer by layer 224 us, this pass 104 us (1.4 GB of weights through
+// inputs: layer by layer 224 us, this pass 104-108 us (1.4 GB of weights through
 // the L1s at 14 TB/s, 35 % of the matrix cores' rate); 32 environments by 8
 // waves with every layer in a region of its own 157 us.  Twice or four times
 // the weight fragments in flight, and a raised wave priority: no change.
@@ -1600,6 +1639,7 @@ void wide_infer_kernel(const FusedArgs a) {
     float *s_bias = reinterpret_cast<float *>(lds + a.lds_bias);
     float *s_head = reinterpret_cast<float *>(lds + a.lds_head);
     const FusedNet &N = a.net[net];
+    ActorNoise noise{};
     {
         // hidden biases (16-byte aligned, at most 4 NT wide), output biases and
         // log-std, and the block's observation rows, in one round of loads
@@ -1614,7 +1654,10 @@ void wide_infer_kernel(const FusedArgs a) {
         const __amdgpu_buffer_rsrc_t rl = make_rsrc(a.logstd, static_cast<long long>(a.A) * 4);
         const float vo = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, tid < n_out ? tid * 4 : kOutside, 0, 0));
         const float vl = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rl, tid < a.A ? tid * 4 : kOutside, 0, 0));
-        gather_rows<R, NT>(a, nullptr, rows, reinterpret_cast<uint16_t *>(lds + a.lds_x), a.kpad + 8, wave, lane, m0);
+        gather_rows<R, NT>(a, nullptr, rows, reinterpret_cast<uint16_t *>(lds + a.lds_x), a.kpad + 8, wave, lane, m0,
+                           [&]() {
+                               if (net == 0) noise = actor_noise<NT / R>(a, m0, rows);
+                           });
 #pragma unroll
         for (int l = 0; l < kMaxHidden; ++l)
             if (l < a.L && 4 * tid < a.H[l]) *reinterpret_cast<u32x4 *>(s_bias + a.bias_off[l] + 4 * tid) = vb[l];
@@ -1630,7 +1673,7 @@ void wide_infer_kernel(const FusedArgs a) {
     else
         wide_layers<1>(a, N, lds, s_bias, w_out, n_out, wave, lane);
     if (a.L == 2) __syncthreads();
-    infer_head<NT / R>(a, net, reinterpret_cast<const uint16_t *>(lds), w_out, s_head, m0, rows);
+    infer_head<NT / R>(a, net, reinterpret_cast<const uint16_t *>(lds), w_out, s_head, noise, m0, rows);
 }
 
 size_t align16(size_t v) { return (v + 15) & ~static_cast<size_t>(15); }
@@ -1718,12 +1761,12 @@ bool width_splits(int width, int NW, int SB, bool wide_ok, int regs = 320) {
 }
 
 // LDS plan of wide_infer_kernel; returns the total bytes, 0 when the network
-// does not fit it: a first layer of whole tiles with the inputs no larger than
-// one, a second layer of one or two feature blocks per wave, later layers that
-// split over the waves, and the output layer's per-lane slice.
+// does not fit it: a first layer of whole tiles, a second layer of one or two
+// feature blocks per wave, later layers that split over the waves, and the
+// output layer's per-lane slice.
 size_t wide_layout(int L, const int *H, int kpad, FusedArgs *a) {
     constexpr int R = kWideRows, NW = kWideThreads / 64, SB = R / 32, KP = kWideThreads / R;
-    if (L < 2 || H[0] % kWideTile != 0 || kpad > kWideTile) return 0;
+    if (L < 2 || H[0] % kWideTile != 0) return 0;
     if (H[1] != 32 * NW && H[1] != 64 * NW) return 0;
     for (int l = 2; l < L; ++l)
         if (!width_splits(H[l], NW, SB, false, layer_regs(2, SB))) return 0;
@@ -1733,7 +1776,9 @@ size_t wide_layout(int L, const int *H, int kpad, FusedArgs *a) {
     const size_t tile = P(kWideTile);
     size_t w_off = 0;
     for (int l = 1; l < L; ++l) w_off = std::max(w_off, P(H[l]));
-    const size_t region = std::max(H[0] / kWideTile * tile, w_off + static_cast<size_t>(kFusedMaxAct) * (Hl + 4) * 4);
+    const size_t x_off = (H[0] / kWideTile - 1) * tile;   // inputs wider than a tile reach past the last one
+    const size_t region =
+        std::max({x_off + std::max(tile, P(kpad)), w_off + static_cast<size_t>(kFusedMaxAct) * (Hl + 4) * 4});
     int bias_off[kMaxHidden] = {0};
     size_t nb = 0;
     for (int l = 0; l < L; ++l) {
@@ -1743,7 +1788,7 @@ size_t wide_layout(int L, const int *H, int kpad, FusedArgs *a) {
     const size_t total = region + nb * 4 + 2 * kFusedMaxAct * 4;
     if (total > static_cast<size_t>(kMaxLdsBytes)) return 0;
     if (a) {
-        a->lds_x = static_cast<int>((H[0] / kWideTile - 1) * tile);
+        a->lds_x = static_cast<int>(x_off);
         a->lds_w = static_cast<int>(w_off);
         a->lds_bias = static_cast<int>(region);
         a->lds_head = static_cast<int>(region + nb * 4);

@@ -21,7 +21,8 @@ pytestmark = pytest.mark.gpu
 NARROW = [(48, 12, (64, 64), 64), (45, 10, (64,), 1), (235, 4, (256, 128, 64), 33), (7, 16, (64, 256, 128, 64), 31),
           (33, 12, (128, 64), 97)]
 WIDE = [(235, 12, (1024, 512, 256), 65), (48, 8, (1024, 512, 256), 1), (225, 16, (768, 256, 128), 130),
-        (256, 2, (512, 512, 512), 63), (17, 12, (1024, 512), 64), (100, 6, (256, 512, 256, 512), 200)]
+        (256, 2, (512, 512, 512), 63), (17, 12, (1024, 512), 64), (100, 6, (256, 512, 256, 512), 200),
+        (300, 12, (1024, 512, 256), 65), (500, 8, (768, 256, 128), 31)]   # inputs past the last tile
 ODD = [(225, 12, (512, 256, 128), 100), (5, 12, (128, 128), 32), (57, 14, (256, 128), 40)]
 
 
