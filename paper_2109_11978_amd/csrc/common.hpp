@@ -110,8 +110,11 @@ struct GemmProblem {
 };
 
 // Output tile shapes (rows x columns per workgroup of 4 wave64s).
-enum GemmTileShape { kTile128x128 = 0, kTile64x128 = 1, kTile128x64 = 2, kTile64x64 = 3, kNumTileShapes = 4 };
-inline int tile_rows(int t) { return (t == kTile64x128 || t == kTile64x64) ? 64 : 128; }
+enum GemmTileShape { kTile128x128 = 0, kTile64x128 = 1, kTile128x64 = 2, kTile64x64 = 3, kNumTileShapes = 4,
+                     // bf16 weight gradient of wide networks, 8 waves: not tuned, taken in
+                     // place of 128 x 128 by a rule
+                     kTile256x128 = 4 };
+inline int tile_rows(int t) { return t == kTile256x128 ? 256 : (t == kTile64x128 || t == kTile64x64) ? 64 : 128; }
 inline int tile_cols(int t) { return (t == kTile128x64 || t == kTile64x64) ? 64 : 128; }
 
 struct GemmArgs {
@@ -119,6 +122,9 @@ struct GemmArgs {
     int count;
     int total_tiles;
     int tile;    // GemmTileShape shared by every problem of the launch
+    // kTile256x128: every `group` consecutive problems share their split count,
+    // and all their tiles of one split come together; else unused
+    int group;
 };
 
 // k-slab depth per operand type (shared with the host planner).
@@ -126,6 +132,8 @@ template <typename T> struct GemmTile;
 template <> struct GemmTile<uint16_t> { static constexpr int BK = 64; };
 template <> struct GemmTile<float> { static constexpr int BK = 32; };
 
+// Whether every problem's operands qualify for the buffer-load path.
+bool gemm_fast(Precision prec, const GemmArgs &args);
 hipError_t launch_gemm(Precision prec, int a_mode, int b_mode, int epi, const GemmArgs &args,
                        hipStream_t stream);
 

@@ -145,6 +145,23 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base, long long b
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), static_cast<short>(0), n, 0x00020000);
 }
 
+// An operand of the current tile: base, bytes up to its last valid row, pitch.
+struct OperandDesc {
+    int lo, hi, bytes, ld;
+    __device__ inline void set(const void *base, int rows, int pitch, size_t esz) {
+        const uint64_t p = reinterpret_cast<uintptr_t>(base);
+        const long long n = static_cast<long long>(rows) * pitch * static_cast<int>(esz);
+        lo = __builtin_amdgcn_readfirstlane(static_cast<int>(p));
+        hi = __builtin_amdgcn_readfirstlane(static_cast<int>(p >> 32));
+        bytes = __builtin_amdgcn_readfirstlane(n > 0x7FFFFFFFLL ? 0x7FFFFFFF : static_cast<int>(n < 0 ? 0 : n));
+        ld = __builtin_amdgcn_readfirstlane(pitch);
+    }
+    __device__ inline __amdgpu_buffer_rsrc_t rsrc() const {
+        const uint64_t p = static_cast<uint32_t>(lo) | static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32;
+        return make_rsrc(reinterpret_cast<const void *>(p), bytes);
+    }
+};
+
 // bf16 operands stored transposed (MODE 1) are staged without any register
 // transpose: each 16-byte global vector (8 consecutive rows at one k) goes to
 // LDS as is, in a k-major tile [BK][ROWS] whose 16-byte columns are XOR-
@@ -153,26 +170,26 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *base, long long b
 // transposed reads of a half-wave on distinct banks.
 template <int ROWS>
 __device__ inline int tr_swz(int k) {
-    return ROWS == 128 ? ((k & 3) << 2) : (((k >> 1) & 1) << 2);
+    return ROWS >= 128 ? ((k & 3) << 2) : (((k >> 1) & 1) << 2);
 }
 template <int ROWS>
 __device__ inline int tr_index(int k, int r) {  // element (k, r) of a k-major tile
     return k * ROWS + ((((r >> 3) ^ tr_swz<ROWS>(k))) << 3) + (r & 7);
 }
 
-template <typename T, int MODE, int ROWS, int BK>
+template <typename T, int MODE, int ROWS, int BK, int NTHR = kThreads>
 struct TileLoader {
     static constexpr int VEC = 16 / sizeof(T);
     static constexpr int PITCH = BK + VEC;
     // TR: bf16 transposed operand staged k-major (no register transpose).
     static constexpr bool TR = MODE == 1 && sizeof(T) == 2;
-    static_assert(!TR || ROWS == 64 || ROWS == 128, "k-major tiles have 64 or 128 rows");
+    static_assert(!TR || ROWS == 64 || ROWS % 128 == 0, "k-major tiles have 64 rows or a multiple of 128");
     // Elements of one LDS tile of this operand.
     static constexpr int ELEMS = TR ? BK * ROWS : ROWS * PITCH;
     // MODE 0 and TR: units are 16-byte vectors (along k, resp. along rows);
     // float32 MODE 1: VEC x VEC blocks transposed in registers.
     static constexpr int UNITS = (MODE == 0 || TR) ? ROWS * BK / VEC : (ROWS / VEC) * (BK / VEC);
-    static constexpr int NT = UNITS < kThreads ? UNITS : kThreads;
+    static constexpr int NT = UNITS < NTHR ? UNITS : NTHR;
     static constexpr int PER = UNITS / NT;
     static constexpr int REGS = (MODE == 0 || TR) ? PER : PER * VEC;
     static_assert(UNITS % NT == 0, "tile units must divide evenly");
@@ -198,7 +215,7 @@ struct TileLoader {
     // read as zeros.  MODE 1 rows past R read neighbouring features, which
     // only reach outputs the epilogue discards.
     __device__ inline void setup(int ld, int r0, int t) {
-        if (NT < kThreads && (t < 0 || t >= NT)) return;
+        if (NT < NTHR && (t < 0 || t >= NT)) return;
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
             const int u = t + p * NT;
@@ -228,30 +245,34 @@ struct TileLoader {
     // zeros.
     static constexpr int kOutside = 0x7FFFFFF0;
     __device__ inline void load_fast(__amdgpu_buffer_rsrc_t rs, int ld, int k0, int kend, int t) {
-        if (NT < kThreads && (t < 0 || t >= NT)) return;
+        load_fast(rs, ld, k0, kend, t, voff);
+    }
+    // the same with another set's offsets
+    __device__ inline void load_fast(__amdgpu_buffer_rsrc_t rs, int ld, int k0, int kend, int t, const int (&vo_at)[PER]) {
+        if (NT < NTHR && (t < 0 || t >= NT)) return;
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
             // k0 and ld are uniform; readfirstlane keeps the scalar offset in an
             // SGPR (the compiler cannot always prove uniformity by itself)
             if constexpr (MODE == 0) {
                 const int so = __builtin_amdgcn_readfirstlane(k0 * static_cast<int>(sizeof(T)));
-                const int vo = k0 + kofs[p] < kend ? voff[p] : kOutside;
+                const int vo = k0 + kofs[p] < kend ? vo_at[p] : kOutside;
                 r[p] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo, so, 0);
             } else if constexpr (TR) {
                 const int so = __builtin_amdgcn_readfirstlane(k0 * ld * static_cast<int>(sizeof(T)));
-                r[p] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff[p], so, 0);
+                r[p] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo_at[p], so, 0);
             } else {
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) {
                     const int so = __builtin_amdgcn_readfirstlane((k0 + e) * ld * static_cast<int>(sizeof(T)));
-                    r[p * VEC + e] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff[p], so, 0);
+                    r[p * VEC + e] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo_at[p], so, 0);
                 }
             }
         }
     }
 
     __device__ inline void load(const T *src, int ld, int R, int r0, int k0, int kend, int t, bool vec_ok) {
-        if (NT < kThreads && (t < 0 || t >= NT)) return;
+        if (NT < NTHR && (t < 0 || t >= NT)) return;
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
             const int u = t + p * NT;
@@ -276,7 +297,7 @@ struct TileLoader {
     }
 
     __device__ inline void store(T *lds, int t) const {
-        if (NT < kThreads && (t < 0 || t >= NT)) return;
+        if (NT < NTHR && (t < 0 || t >= NT)) return;
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
             const int u = t + p * NT;
@@ -302,7 +323,7 @@ struct TileLoader {
     // TR only: add this thread's staged vectors (8 rows each, the same 8
     // rows for every unit of the thread) to its per-row partial sums.
     __device__ inline void accumulate_rows(float (&acc)[VEC], int t) const {
-        if (NT < kThreads && (t < 0 || t >= NT)) return;
+        if (NT < NTHR && (t < 0 || t >= NT)) return;
 #pragma unroll
         for (int p = 0; p < PER; ++p)
 #pragma unroll
@@ -386,6 +407,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(const GemmArgs args) 
     constexpr int VEC = 16 / sizeof(T);
     constexpr int PITCH = BK + VEC;
     constexpr int KC = 2 * VEC;  // k covered by one 16-byte read in each lane-half
+    constexpr bool DESC = FAST && EPI == kEpiPartial && sizeof(T) == 2;
     using LA = TileLoader<T, AMODE, BM, BK>;
     using LB = TileLoader<T, BMODE, BN, BK>;
     // Split the threads between the two operands when neither needs all of them.
@@ -434,10 +456,27 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(const GemmArgs args) 
             }
         }
     };
+    // bf16 weight gradient: the tile's operands in scalar registers for the whole
+    // k-loop.  readfirstlane keeps the compiler from reading them again from
+    // the kernel arguments in every slab (a scalar load's latency each, on the
+    // path between two barriers).
+    OperandDesc da, db;
+    auto describe = [&](int pi, int kend) {
+        if constexpr (DESC) {
+            const GemmProblem &Q = args.p[pi];
+            da.set(Q.A, AMODE == 0 ? Q.M : kend, Q.lda, sizeof(T));
+            db.set(Q.B, BMODE == 0 ? Q.N : kend, Q.ldb, sizeof(T));
+        }
+    };
     // Loads slab kt of a tile into a staging set.  With a second B operand
     // the k-range runs twice: slabs nkb .. 2 nkb - 1 pair A's slabs 0 ..
     // nkb - 1 with B2 (slabs past the end read zeros either way).
     auto load_slab = [&](int pi, int m0, int n0, int kbeg, int kend, LA &la, LB &lb, int kt) {
+        if constexpr (DESC) {
+            la.load_fast(da.rsrc(), da.ld, kbeg + kt * BK, kend, tid);
+            lb.load_fast(db.rsrc(), db.ld, kbeg + kt * BK, kend, tid - B_OFF);
+            return;
+        }
         const GemmProblem &Q = args.p[pi];
         const int nkb = (kend - kbeg + BK - 1) / BK;
         const bool second = Q.B2 != nullptr && kt >= nkb;
@@ -517,6 +556,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(const GemmArgs args) 
     int pi, m0, n0, split, tn, kbeg, kend;
     decode_tile<BM, BN, BK>(args, d, pi, m0, n0, split, tn, kbeg, kend);
     setup_loaders(pi, m0, n0);
+    describe(pi, kend);
     // On the FAST path every load and LDS store of the loop is unconditional:
     // slabs past the end read as zeros (their offsets fall outside the buffer
     // resources) and land in a buffer nobody reads again.  Conditional loads
@@ -652,6 +692,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(const GemmArgs args) 
         if (has_next) {
             decode_tile<BM, BN, BK>(args, dn, npi, nm0, nn0, nsplit, ntn, nkbeg, nkend);
             setup_loaders(npi, nm0, nn0);
+            describe(npi, nkend);
             load_slab(npi, nm0, nn0, nkbeg, nkend, la0, lb0, 0);
         }
 
@@ -728,6 +769,174 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(const GemmArgs args) 
         // the staged accumulators are read before the next tile's slab 0 goes
         // into the same memory
         __syncthreads();
+    }
+}
+
+// Weight gradient (bf16) of wide networks: 256 x 128 tiles, 8 waves of 64 x 64
+// each, one workgroup per CU, in place of 128 x 128 tiles with the same split
+// of the samples (so the same partial sums, bit for bit).
+//
+// What bounds it: with 128 x 128 tiles the operands.  At [1024, 512, 256] with
+// 235 inputs and 49152 samples (464 tiles, 700 MB of operands) the CUs that
+// hold one workgroup run ahead of those that hold two, the tiles that share
+// an operand drift apart, and L2 fetched 1.69 GB in 301-323 us, the 5.4 TB/s
+// that reads beyond L2 reach.  Here all 240 workgroups run at the same rate,
+// each reads half as much of one operand, and the tiles of one split of one
+// network, which use every operand once, lie on one XCD: 0.91 GB, 235-248 us
+// (the whole epoch 7.50 -> 6.72 ms).  What bounds it now is the LDS: 256
+// transposing reads per 64 samples at half the LDS rate take 2048 of the
+// loop's 3000 cycles (199 us without the global loads).  So the fragments are
+// read one k-step ahead, across the barrier into the next slab (three
+// buffers), and the operands' descriptors stay in scalar registers.  Measured
+// and left: four waves of 128 x 64 (fewer reads, but they spill: 472 us),
+// transposing in registers for full-rate reads (291 us), the LDS stores in
+// another k-step (253-266 us).
+constexpr int kWideThreads = 512;
+constexpr int kWideM = 256, kWideN = 128;
+constexpr int kWideBufs = 3;
+
+__global__ __launch_bounds__(kWideThreads, 2) void dw_wide_kernel(const GemmArgs args) {
+    using T = uint16_t;
+    constexpr int BK = GemmTile<T>::BK, VEC = 8;
+    constexpr int KCS = BK / 16;                // MFMA k-steps per slab
+    using LA = TileLoader<T, 1, kWideM, BK, kWideThreads>;
+    using LB = TileLoader<T, 1, kWideN, BK, kWideThreads>;
+    constexpr int BUF = LA::ELEMS + LB::ELEMS;
+    __shared__ __attribute__((aligned(16))) T lds[kWideBufs * BUF];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+
+    // workgroup -> (problem, split, tile): a split's tiles of every problem of
+    // a group (one network's layers) come together on one XCD
+    const int bid = xcd_swizzle(blockIdx.x, args.total_tiles);
+    int pi = 0;
+    while (pi + args.group < args.count && bid >= args.p[pi + args.group].tile_begin) pi += args.group;
+    const int last = min(pi + args.group, args.count) - 1;
+    const int begin = args.p[pi].tile_begin;
+    const int end = last + 1 < args.count ? args.p[last + 1].tile_begin : args.total_tiles;
+    const int per_split = (end - begin) / args.p[pi].splits;
+    const int split = __builtin_amdgcn_readfirstlane((bid - begin) / per_split);
+    int rem = bid - begin - split * per_split;
+    while (pi < last && rem >= args.p[pi].tiles_m * args.p[pi].tiles_n) {
+        rem -= args.p[pi].tiles_m * args.p[pi].tiles_n;
+        ++pi;
+    }
+    pi = __builtin_amdgcn_readfirstlane(pi);
+    const GemmProblem &P = args.p[pi];
+    const int tm = __builtin_amdgcn_readfirstlane(rem / P.tiles_n), tn = rem - tm * P.tiles_n;
+    const int m0 = tm * kWideM, n0 = tn * kWideN;
+    const int kbeg = __builtin_amdgcn_readfirstlane(split * P.kps);
+    const int kend = __builtin_amdgcn_readfirstlane(min(P.K, kbeg + P.kps));
+    const int nk = __builtin_amdgcn_readfirstlane((kend - kbeg + BK - 1) / BK);
+    const bool do_rowsum = tn == 0;
+
+    OperandDesc da, db;
+    da.set(P.A, kend, P.lda, sizeof(T));
+    db.set(P.B, kend, P.ldb, sizeof(T));
+    LA la[2];
+    LB lb[2];
+    la[0].setup(da.ld, m0, tid);
+    lb[0].setup(db.ld, n0, tid);
+    // slab kt into a staging set (both with the first set's offsets); past the
+    // end it reads zeros
+    auto load = [&](int kt, auto set) {
+        constexpr int S = decltype(set)::value;
+        la[S].load_fast(da.rsrc(), da.ld, kbeg + kt * BK, kend, tid, la[0].voff);
+        lb[S].load_fast(db.rsrc(), db.ld, kbeg + kt * BK, kend, tid, lb[0].voff);
+    };
+    float rows8[VEC] = {};
+    auto store = [&](auto set, auto buf) {
+        constexpr int S = decltype(set)::value, Q = decltype(buf)::value;
+        la[S].store(lds + Q * BUF, tid);
+        lb[S].store(lds + Q * BUF + LA::ELEMS, tid);
+        if (do_rowsum) la[S].accumulate_rows(rows8, tid);
+    };
+    floatx16 acc[2][2] = {};
+    u32x4 fa[2][2], fb[2][2];
+    auto frags = [&](auto buf, int kc) {
+        constexpr int Q = decltype(buf)::value;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            fa[kc & 1][i] = frag_tr<kWideM>(lds + Q * BUF, wm * 64 + i * 32, kc, lane);
+            fb[kc & 1][i] = frag_tr<kWideN>(lds + Q * BUF + LA::ELEMS, wn * 64 + i * 32, kc, lane);
+        }
+    };
+    // slab kt out of buffer kt % 3, while slab kt + 2 goes from its registers
+    // into the buffer of slab kt - 1 and slab kt + 3 loads
+    auto step = [&](int kt, auto phase) {
+        constexpr int PH = decltype(phase)::value;   // kt mod 6
+        using Cur = std::integral_constant<int, PH % 3>;
+        using Next = std::integral_constant<int, (PH + 1) % 3>;
+        load(kt + 3, std::integral_constant<int, (PH + 1) % 2>());
+#pragma unroll
+        for (int kc = 0; kc < KCS; ++kc) {
+            if (kc + 1 < KCS)
+                frags(Cur(), kc + 1);
+            else
+                frags(Next(), 0);
+            if (kc == 1) store(std::integral_constant<int, PH % 2>(), std::integral_constant<int, (PH + 2) % 3>());
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) Mma<T>::mac(acc[i][j], fa[kc & 1][i], fb[kc & 1][j]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+    };
+    using std::integral_constant;
+    load(0, integral_constant<int, 0>());
+    load(1, integral_constant<int, 1>());
+    store(integral_constant<int, 0>(), integral_constant<int, 0>());
+    load(2, integral_constant<int, 0>());
+    store(integral_constant<int, 1>(), integral_constant<int, 1>());
+    __syncthreads();
+    frags(integral_constant<int, 0>(), 0);
+    for (int kt = 0; kt < nk; kt += 6) {
+        step(kt, integral_constant<int, 0>());
+        if (kt + 1 >= nk) break;
+        step(kt + 1, integral_constant<int, 1>());
+        if (kt + 2 >= nk) break;
+        step(kt + 2, integral_constant<int, 2>());
+        if (kt + 3 >= nk) break;
+        step(kt + 3, integral_constant<int, 3>());
+        if (kt + 4 >= nk) break;
+        step(kt + 4, integral_constant<int, 4>());
+        if (kt + 5 >= nk) break;
+        step(kt + 5, integral_constant<int, 5>());
+    }
+
+    // partial sums: a lane holds a column of 16 rows per block, so each store
+    // writes two rows' 128 bytes
+    const int lrow = lane & 31, lhi = lane >> 5;
+    float *c = static_cast<float *>(P.C) + split * P.c_split_stride;
+    const __amdgpu_buffer_rsrc_t c_rs = make_rsrc(c, static_cast<long long>(P.M) * P.ldc * 4);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int col = n0 + wn * 64 + j * 32 + lrow;
+        const int vo = col < P.N ? (lhi * 4 * P.ldc + col) * 4 : 0x7FFFFFF0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = m0 + wm * 64 + i * 32 + (r >> 2) * 8 + (r & 3);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][r]), c_rs, vo, row * P.ldc * 4, 0);
+            }
+    }
+    if (do_rowsum) {
+        // as in gemm_kernel: every thread summed the same 8 rows in every slab
+        constexpr int GROUPS = kWideM / VEC, PER_GROUP = kWideThreads / GROUPS;
+        float *red = reinterpret_cast<float *>(lds);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) red[tid * VEC + e] = rows8[e];
+        __syncthreads();
+        if (tid < kWideM && m0 + tid < P.M) {
+            const int gq = tid / VEC, e = tid % VEC;
+            float v = 0.0f;
+            for (int q = 0; q < PER_GROUP; ++q) v += red[(gq + GROUPS * q) * VEC + e];
+            P.rowsum[static_cast<long long>(split) * P.M + m0 + tid] = v;
+        }
     }
 }
 
@@ -814,11 +1023,22 @@ hipError_t launch_typed(int a_mode, int b_mode, int epi, const GemmArgs &args, h
         case kTile64x128: return launch_tiled<T, 64, 128>(a_mode, b_mode, epi, args, s);
         case kTile128x64: return launch_tiled<T, 128, 64>(a_mode, b_mode, epi, args, s);
         case kTile64x64: return launch_tiled<T, 64, 64>(a_mode, b_mode, epi, args, s);
+        case kTile256x128:
+            if constexpr (sizeof(T) == 2)
+                if (a_mode == 1 && b_mode == 1 && epi == kEpiPartial && args.group > 0 && all_fast<T>(args)) {
+                    hipLaunchKernelGGL(dw_wide_kernel, dim3(args.total_tiles), dim3(kWideThreads), 0, s, args);
+                    return hipGetLastError();
+                }
+            return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
 }
 
 }  // namespace
+
+bool gemm_fast(Precision prec, const GemmArgs &args) {
+    return prec == kBF16 ? all_fast<uint16_t>(args) : all_fast<float>(args);
+}
 
 hipError_t launch_gemm(Precision prec, int a_mode, int b_mode, int epi, const GemmArgs &args, hipStream_t s) {
     if (args.total_tiles <= 0) return hipSuccess;

@@ -623,11 +623,28 @@ struct DwPlan {
     ReduceArgs red{};
 };
 
+// Weight-gradient plan with 128 x 128 tiles (bf16, every operand on the
+// buffer-load path): the same splits in tiles of 256 x 128, one workgroup per
+// CU, where those fill at least seven eighths of the CUs and need no second
+// round.  Widths of 256 and more pair their tiles ([1024, 512, 256]: 464 -> 240
+// tiles, 301-323 -> 235-248 us for 49152 samples); narrower layers leave half
+// of a paired tile empty ([512, 256, 128]: 510 -> 306 tiles, two rounds).
+void pair_dw_tiles(GemmArgs &args, int group, Precision prec) {
+    if (prec != kBF16 || args.tile != kTile128x128 || !gemm_fast(prec, args)) return;
+    constexpr int cus = kResidentSlots / 2;
+    GemmArgs wide{};
+    wide.tile = kTile256x128;
+    wide.group = group;
+    for (int i = 0; i < args.count; ++i) add_problem(wide, args.p[i], gemm_bk(prec));
+    if (wide.total_tiles <= cus && 8 * wide.total_tiles >= 7 * cus) args = wide;
+}
+
 // kps_layer (optional, per layer 0..L, both networks): samples per split in
 // place of the run's own choice where positive.  Problems are added network
-// by network, layer by layer: problem net * (L + 1) + l.
+// by network, layer by layer: problem net * (L + 1) + l.  pair: pair the tiles
+// where pair_dw_tiles does.
 DwPlan build_dw(const ppo_ctx *c, const WsPlan &w, void *ws, int M, const TileChoice &tc,
-                const int *kps_layer = nullptr) {
+                const int *kps_layer = nullptr, bool pair = true) {
     const NetLayout &g = c->g;
     const int L = g.L;
     DwPlan d;
@@ -693,6 +710,7 @@ DwPlan build_dw(const ppo_ctx *c, const WsPlan &w, void *ws, int M, const TileCh
         }
     }
     ++d.n_launch;
+    if (d.n_launch == 1 && !kps_layer && pair) pair_dw_tiles(d.launch[0], L + 1, c->prec);
     plan_reduce(d.red);
     return d;
 }
@@ -844,7 +862,12 @@ int ensure_tuned(const ppo_ctx *cc, const ppo_params *p, const WsPlan &w, void *
                     TileChoice tc;
                     tc.tile = tile;
                     tc.rounds = rounds;
-                    DwPlan d = build_dw(c, w, ws, rows, tc);
+                    // Timed as plain tiles, so that pairing, which changes no
+                    // result, leaves a clear choice of the split, which does,
+                    // as it is.  Near ties go to the candidate that will run
+                    // paired ([1024, 512, 256], 49152 samples: 312-314 us with
+                    // four splits against 314-320 with two, and 250 paired).
+                    DwPlan d = build_dw(c, w, ws, rows, tc, nullptr, false);
                     ReduceArgs &red = d.red;
                     red.grad = grad_scratch;
                     red.sumsq_partials = reinterpret_cast<double *>(wsp(ws, w.sumsq));
@@ -868,6 +891,7 @@ int ensure_tuned(const ppo_ctx *cc, const ppo_params *p, const WsPlan &w, void *
                                 },
                                 reps, ms),
                             "autotune weight gradient");
+                    if (build_dw(c, w, ws, rows, tc).launch[0].tile == kTile256x128) ms *= 0.96f;
                     if (ms < best) {
                         best = ms;
                         t.site[kSiteDw] = tc;
