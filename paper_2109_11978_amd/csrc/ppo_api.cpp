@@ -11,6 +11,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -414,6 +415,7 @@ struct ppo_ctx {
     std::map<std::vector<uint64_t>, hipGraphExec_t> graphs;
     std::vector<std::vector<uint64_t>> graph_order;  // insertion order for eviction
     std::map<int, Tuning> tuned;                      // GEMM rows -> measured tile choices
+    std::set<int> untiled;   // rows whose inference ran as a narrow, wide or odd-width pass
     bool keep_packed = false;                         // PPO_OPT_KEEP_PACKED
 };
 
@@ -1451,6 +1453,13 @@ int ppo_rollout_infer(const ppo_ctx *c, void *stream, const ppo_params *p, const
         a.NT = fsh.threads;
         a.per_cu = fsh.per_cu;
         PPO_HIP(launch_fused_infer(a, s), "fused inference");
+        // ppo_fused_infer_shape reports the general pass alone; for the others
+        // ppo_ctx_tuning keeps answering
+        if (fsh.per_cu < 0 || fsh.threads < 256 || w.kpad % 16 != 0) {
+            ppo_ctx *cc = const_cast<ppo_ctx *>(c);
+            std::lock_guard<std::mutex> lk(cc->mu);
+            cc->untiled.insert(N);
+        }
         return PPO_OK;
     }
     note_ws_used(ws, ws_bytes);
@@ -2297,10 +2306,13 @@ int ppo_ctx_tuning(const ppo_ctx *c, int32_t rows, int32_t update, int32_t *choi
     ppo_ctx *cc = const_cast<ppo_ctx *>(c);
     std::lock_guard<std::mutex> lk(cc->mu);
     auto it = cc->tuned.find(update ? -rows : rows);
-    if (it == cc->tuned.end()) return fail(PPO_E_SHAPE, "no tile choice recorded for %d rows", rows);
+    const bool known = it != cc->tuned.end();
+    if (!known && (update || !cc->untiled.count(rows)))
+        return fail(PPO_E_SHAPE, "no tile choice recorded for %d rows", rows);
+    const Tuning t = known ? it->second : Tuning{};
     for (int i = 0; i < kNumSites; ++i) {
-        choices[2 * i] = it->second.site[i].tile;
-        choices[2 * i + 1] = it->second.site[i].rounds;
+        choices[2 * i] = t.site[i].tile;
+        choices[2 * i + 1] = t.site[i].rounds;
     }
     return PPO_OK;
 }

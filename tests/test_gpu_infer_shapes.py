@@ -61,3 +61,21 @@ def test_infer_shapes(D, A, H, N, monkeypatch):
     assert_close("logp", got["logp"], ref["logp"], TOL["fp32"])
     only = infer((D, A, H), theta, obs, d, True, monkeypatch, value_only=True)
     assert np.array_equal(only["values"], got["values"])
+
+
+@pytest.mark.parametrize("D,A,H", [(48, 12, (64, 64)), (235, 12, (1024, 512, 256)), (5, 12, (128, 128))])
+def test_tuning_answers_without_tiles(D, A, H):
+    """The tile query works after inference of a network for which
+    fused_infer_shape reports no fused block, and not before."""
+    d = require_gpu()
+    net = synth.NetShape(D, A, H)
+    ctx = ppo.Context(D, A, H, "bf16")
+    assert ctx.fused_infer_shape() == (0, 0)
+    params = ppo.Params(ctx, synth.xavier_theta(net, seed=3, logstd=-0.25), device=d)
+    with pytest.raises(ppo.PPOError):
+        ctx.tuning(40, False)
+    ppo.ppo_rollout_infer(ctx, params, dev(synth.rollout.gaussian_like((40, D), seed=5), d), t=0, seed=1,
+                          iteration=0, ws=ctx.new_workspace(N=40), values=torch.empty(40, device=d))
+    assert set(ctx.tuning(40, False)) == {f"forward_{l + 1}" for l in range(len(H))}
+    with pytest.raises(ppo.PPOError):
+        ctx.tuning(41, False)
