@@ -660,7 +660,7 @@ __device__ __forceinline__ void head_pass(const FusedArgs &a, const FusedNet &N,
 #pragma unroll
         for (int j = 0; j < NO; ++j) {
             g[j] = g_lp * z[j] * inv_sig[j];
-            sums[5 + j] = g_lp * (z[j] * z[j] - 1.0f);
+            sums[5 + j] = g_lp * __builtin_fmaf(z[j], z[j], -1.0f);   // one rounding (see head_mfma)
         }
     } else {
         const float V = o[0];
@@ -838,7 +838,9 @@ __device__ __forceinline__ void head_mfma(const FusedArgs &a, const FusedNet &N,
             for (int t = 0; t < 8; ++t) {
                 const int j = 8 * (t >> 2) + 4 * half + (t & 3);
                 g8[t] = g_lp * z[t] * inv_sig[t];
-                sums[5 + j] = g_lp * (z[t] * z[t] - 1.0f);
+                // one rounding: z^2 rounded by itself (the log-density's own
+                // product, if the compiler shared it) cancels against 1 near |z| = 1
+                sums[5 + j] = g_lp * __builtin_fmaf(z[t], z[t], -1.0f);
             }
         } else {
             // the value is output 0: lane half 0, first accumulator

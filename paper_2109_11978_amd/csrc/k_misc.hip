@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kHeadThreads) void head_loss_kernel(const HeadLossA
                 float gm = 0.0f;
                 if (j < A) {
                     gm = g_lp * z[j] * expf(-a.logstd[j]);
-                    dls[j] = g_lp * (z[j] * z[j] - 1.0f);
+                    dls[j] = g_lp * __builtin_fmaf(z[j], z[j], -1.0f);
                     s_out[i][j] = gm;
                 }
                 dha[j] = Elem<T>::from_f(gm);
