@@ -65,10 +65,13 @@ __device__ inline float hi_f(uint32_t w) { return __uint_as_float(w & 0xFFFF0000
 // median of (e^z - 1, z, 0); ELU'(z) is 1 for h > 0 and h + 1 = e^z otherwise,
 // i.e. min(h + 1, 1).
 __device__ inline float elu(float v) { return __builtin_amdgcn_fmed3f(__expf(v) - 1.0f, v, 0.0f); }
-// The same with the sign test of those epilogues, equal to them bit for bit (for
-// 0 < z < 3e-4 the rounded e^z - 1 may be the smaller of the two, and the
-// median then takes it: up to one bf16 ulp off).  The narrow and wide inference
-// passes use it; the older passes keep the median's bits.
+// The same with the sign test of those epilogues, equal to them bit for bit.  For
+// 0 < z < 3e-4 the rounded e^z - 1, a multiple of 2^-24, may be the smaller of
+// the two, and the median then takes it: about 6e-8 off at most, which is one
+// bf16 ulp of a z above 1e-5, 8 of one above 1e-6 and all of one below 6e-8.
+// Inference of every network but those that the general block has always run
+// (a multiple of 16 inputs once padded to 8) uses the sign test; the older passes
+// keep the median's bits.
 __device__ inline float elu_select(float v) { return v > 0.0f ? v : __expf(v) - 1.0f; }
 __device__ inline float delu(float h) { return fminf(h + 1.0f, 1.0f); }
 
@@ -1452,12 +1455,12 @@ __device__ __forceinline__ void infer_head(const FusedArgs &a, int net, const ui
 // value.  Same draws, formulas and float64 log-density as the
 // layer-by-layer sampling kernel; only the output layer's summation order
 // differs.
-template <int R, int NT, int WPE>
+// SEL: the hidden layers round as the layer-by-layer GEMM epilogues do (elu_select).
+template <int R, int NT, int WPE, bool SEL>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void fused_infer_kernel(const FusedArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int KP = NT / R;
-    constexpr bool SEL = NT == kNarrowThreads;
     const bool both = a.net_mask == 3;
     int net = a.net_mask == 1 ? 0 : 1, sblk = static_cast<int>(blockIdx.x);
     if (both && !net_block(static_cast<int>(blockIdx.x), a.blocks, net, sblk)) return;
@@ -2072,18 +2075,32 @@ hipError_t launch_fused_infer(FusedArgs a, hipStream_t s) {
                               : fused_layout(a.L, a.H, a.kpad, a.A, a.R, a.NT, &a);
     if (bytes == 0) return hipErrorInvalidValue;
     a.blocks = fused_blocks(a.M, a.R);
+    // The general block's shapes, then the narrow one, each with the median ELU
+    // and with the sign test.  Networks whose input width is no multiple of 16
+    // once padded to 8 ran layer by layer before the general block took them, so
+    // they keep that path's rounding.
+    using InferFn = void (*)(const FusedArgs);
+    static const struct {
+        int rows, threads;
+        InferFn fn[2];
+    } kernels[] = {{64, 512, {&fused_infer_kernel<64, 512, 2, false>, &fused_infer_kernel<64, 512, 2, true>}},
+                   {32, 256, {&fused_infer_kernel<32, 256, 2, false>, &fused_infer_kernel<32, 256, 2, true>}},
+                   {32, 512, {&fused_infer_kernel<32, 512, 2, false>, &fused_infer_kernel<32, 512, 2, true>}},
+                   {64, 256, {&fused_infer_kernel<64, 256, 1, false>, &fused_infer_kernel<64, 256, 1, true>}},
+                   {kNarrowRows, kNarrowThreads,
+                    {&fused_infer_kernel<kNarrowRows, kNarrowThreads, 2, true>,
+                     &fused_infer_kernel<kNarrowRows, kNarrowThreads, 2, true>}}};
     static bool attr_set = false;
     if (!attr_set) {
-        const void *fns[6] = {reinterpret_cast<const void *>(&fused_infer_kernel<64, 512, 2>),
-                              reinterpret_cast<const void *>(&fused_infer_kernel<32, 256, 2>),
-                              reinterpret_cast<const void *>(&fused_infer_kernel<32, 512, 2>),
-                              reinterpret_cast<const void *>(&fused_infer_kernel<64, 256, 1>),
-                              reinterpret_cast<const void *>(&fused_infer_kernel<kNarrowRows, kNarrowThreads, 2>),
-                              reinterpret_cast<const void *>(&wide_infer_kernel)};
-        for (const void *fn : fns) {
-            const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
-            if (e != hipSuccess) return e;
-        }
+        auto raise = [](InferFn fn) {
+            return hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       kMaxLdsBytes);
+        };
+        hipError_t e = raise(&wide_infer_kernel);
+        for (const auto &k : kernels)
+            for (InferFn fn : k.fn)
+                if (e == hipSuccess) e = raise(fn);
+        if (e != hipSuccess) return e;
         attr_set = true;
     }
     const dim3 block(a.NT);
@@ -2092,19 +2109,13 @@ hipError_t launch_fused_infer(FusedArgs a, hipStream_t s) {
         return hipGetLastError();
     }
     const dim3 grid(a.net_mask == 3 ? two_net_grid(a.blocks) : a.blocks);
-    if (a.R == 64 && a.NT == 512)
-        hipLaunchKernelGGL((fused_infer_kernel<64, 512, 2>), grid, block, bytes, s, a);
-    else if (a.R == 32 && a.NT == 256)
-        hipLaunchKernelGGL((fused_infer_kernel<32, 256, 2>), grid, block, bytes, s, a);
-    else if (a.R == 32 && a.NT == 512)
-        hipLaunchKernelGGL((fused_infer_kernel<32, 512, 2>), grid, block, bytes, s, a);
-    else if (a.R == 64 && a.NT == 256)
-        hipLaunchKernelGGL((fused_infer_kernel<64, 256, 1>), grid, block, bytes, s, a);
-    else if (a.R == kNarrowRows && a.NT == kNarrowThreads)
-        hipLaunchKernelGGL((fused_infer_kernel<kNarrowRows, kNarrowThreads, 2>), grid, block, bytes, s, a);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+    const int sel = ((a.D + 7) / 8) & 1;
+    for (const auto &k : kernels)
+        if (a.R == k.rows && a.NT == k.threads) {
+            hipLaunchKernelGGL(k.fn[sel], grid, block, bytes, s, a);
+            return hipGetLastError();
+        }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_fused_update(FusedArgs a, hipStream_t s) {
