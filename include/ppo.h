@@ -42,7 +42,9 @@
  *   - Autotuning: the first call for a given row count (N for inference, M
  *     for the update) times the GEMM tile candidates of every launch site
  *     with HIP events on the caller's stream and waits for them (the only
- *     host synchronisation outside ctx create/destroy); the choice is cached
+ *     host synchronisation outside ctx create/destroy); candidates of one site
+ *     give the same bits (the weight gradients' splits follow a rule, except
+ *     in grouped launches of several runs); the choice is cached
  *     in the context, and in the file named by the environment variable
  *     PPO_TUNE_CACHE if set.  PPO_AUTOTUNE=0 keeps 128 x 128 tiles.
  *     PPO_GEMM_GRID_CAP=0 launches one workgroup per GEMM tile (by default
@@ -375,6 +377,17 @@ int ppo_gemm_check(void *stream, int32_t precision, int32_t a_mode, int32_t b_mo
                    int32_t M, int32_t N, int32_t K, const void *A, int32_t lda, const void *B,
                    int32_t ldb, void *C, int32_t ldc, const float *bias, const void *H, int32_t ldh,
                    float *rowsum, int32_t splits, int32_t tile);
+
+/* Weight-gradient launch of an update step over `rows` mini-batch rows (one
+ * that is not grouped with other runs'): plan[0] = tile shape (as in
+ * ppo_gemm_check), plan[1] = splits in half rounds of resident workgroups,
+ * plan[2] = splits, plan[3] = samples per split, plan[4] = workgroups,
+ * plan[5] = 1 where tiles run in pairs (256 x 128, the same sums).  tile < 0:
+ * the rule's choice, which fixes splits and tile height (a tuned step may take
+ * another width); else this tile and rounds (1, 2 or 4).  capacity >= 6.
+ * Host only. */
+int ppo_weight_grad_plan(const ppo_ctx *ctx, int32_t rows, int32_t tile, int32_t rounds, int32_t *plan,
+                         int32_t capacity);
 
 /* Tile choices recorded for `rows` GEMM rows (update != 0: the update's
  * sites, else inference).  choices[2 s] = tile shape (as in

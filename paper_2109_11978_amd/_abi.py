@@ -83,6 +83,7 @@ EXPORTS = {
     "ppo_update_batched": (c_int32, [POINTER(c_void_p), c_int32, c_void_p, POINTER(Params), POINTER(Batch),
                                      POINTER(c_void_p), c_int32, POINTER(HParams), POINTER(c_void_p),
                                      POINTER(c_void_p), POINTER(c_size_t)]),
+    "ppo_weight_grad_plan": (c_int32, [c_void_p, c_int32, c_int32, c_int32, POINTER(c_int32), c_int32]),
     "ppo_ctx_tuning": (c_int32, [c_void_p, c_int32, c_int32, POINTER(c_int32), c_int32]),
     "ppo_fused_shape": (c_int32, [c_void_p, POINTER(c_int32), POINTER(c_int32)]),
     "ppo_fused_infer_shape": (c_int32, [c_void_p, POINTER(c_int32), POINTER(c_int32)]),

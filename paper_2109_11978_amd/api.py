@@ -142,6 +142,13 @@ class Context:
             out["weight_grad"] = f"{self.TILE_NAMES[arr[16]]} x {arr[17]} half round(s) of splits"
         return out
 
+    def weight_grad_plan(self, rows: int, tile: int = -1, rounds: int = 2) -> Dict[str, int]:
+        """Weight-gradient launch of an update over `rows` mini-batch rows, by
+        the rule or with this tile index and rounds."""
+        arr = (ctypes.c_int32 * 6)()
+        check(_lib().ppo_weight_grad_plan(self.handle, rows, tile, rounds, arr, 6))
+        return dict(zip(("tile", "rounds", "splits", "samples_per_split", "workgroups", "paired"), arr))
+
     def fused_shape(self) -> Tuple[int, int]:
         """(samples, threads) per workgroup of the fused bf16 update pass, or
         (0, 0) when update steps run the layer-by-layer kernels."""

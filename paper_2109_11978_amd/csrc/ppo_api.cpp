@@ -213,6 +213,101 @@ int dw_max_splits(const NetLayout &g, Precision prec, int M) {
     return best;
 }
 
+struct TileChoice {
+    int tile = kTile128x128;
+    int rounds = 2;  // weight-gradient splits: half rounds of resident workgroups (1, 2 or 4)
+};
+
+// What a candidate of the weight gradient costs beyond what all have in common,
+// in us: its longest workgroup's k-slabs, each at a time that depends on the
+// tile and on how many workgroups share a CU (slab: one, two, more) and grows
+// by `far` as the operands outgrow `cache` MB; a start per tile and per
+// workgroup of a CU; and for every split a launch's share and the partials that
+// the reduction reads (per million parameters).  Fitted to 5900 timings of
+// twelve candidates each (GEMM and reduction; 128 to 131072 samples of
+// networks from [64, 64] to [1024, 512, 256] with 12 to 320 inputs): the
+// cheapest by these numbers is the one that timing takes in 86 % (bf16) and
+// 90 % (float32) of the cases, where two timings of one case agree in 92 and
+// 93 %, and it is 0.4 and 0.2 % slower than the fastest on average.
+struct SplitCost {
+    float slab[3][kNumTileShapes];
+    float start[kNumTileShapes], per_wg[kNumTileShapes];
+    float per_split, per_mparam;
+    float cache, far[3];
+};
+constexpr SplitCost kSplitCost[2][2] = {   // [precision][rows off the buffer-load path]
+    {{{{3.10f, 1.87f, 1.73f, 1.11f}, {5.39f, 3.02f, 3.04f, 1.66f}, {9.56f, 5.47f, 5.70f, 2.71f}},
+      {3.91f, 2.76f, 3.90f, 1.16f}, {0.03f, 1.16f, 0.45f, 1.50f}, 0.063f, 2.32f, 58.9f, {0.326f, 0.414f, 0.580f}},
+     {{{2.48f, 2.14f, 1.85f, 1.28f}, {4.60f, 2.68f, 3.08f, 1.86f}, {9.10f, 5.12f, 5.69f, 2.99f}},
+      {13.5f, 7.41f, 11.1f, 9.19f}, {0.16f, 3.25f, 0.02f, 0.45f}, 0.101f, 1.49f, 731.0f, {0.002f, 0.892f, 0.051f}}},
+    {{{{0.995f, 0.541f, 0.662f, 0.553f}, {1.25f, 0.807f, 0.972f, 0.640f}, {1.71f, 1.18f, 1.57f, 0.912f}},
+      {2.73f, 3.70f, 3.71f, 1.03f}, {2.49f, 2.16f, 0.913f, 1.38f}, 0.170f, 1.38f, 86.6f, {0.001f, 0.007f, 0.516f}},
+     {{{1.87f, 1.79f, 1.77f, 1.45f}, {1.26f, 1.65f, 1.42f, 1.22f}, {2.17f, 3.10f, 2.13f, 1.55f}},
+      {4.63f, 3.46f, 2.71f, 1.04f}, {2.60f, 1.29f, 1.84f, 1.35f}, 0.145f, 0.855f, 232.0f, {0.507f, 1.12f, 0.002f}}}};
+static_assert(kFP32 == 0 && kBF16 == 1, "kSplitCost's order");
+
+// Operands of the weight gradient, each once, in MB.
+double dw_operand_mb(const NetLayout &g, Precision prec, int M) {
+    long long width = 0;
+    for (int net = 0; net < 2; ++net)
+        for (int l = 0; l <= g.L; ++l) {
+            int r, c;
+            dw_shape(g, net == 0, l, r, c);
+            width += r + c;
+        }
+    return static_cast<double>(width) * M * (prec == kBF16 ? 2 : 4) / (1 << 20);
+}
+
+bool dw_on_fast_path(Precision prec, int M) { return M % (prec == kBF16 ? 8 : 4) == 0; }
+
+double dw_cost(const NetLayout &g, Precision prec, int M, const TileChoice &tc) {
+    const SplitCost &C = kSplitCost[prec][dw_on_fast_path(prec, M) ? 0 : 1];
+    int splits, kps;
+    dw_splits(g, prec, M, tc.tile, tc.rounds, splits, kps);
+    const int per_cu = cdiv(static_cast<long long>(dw_tiles(g, tc.tile)) * splits, kResidentSlots / 2);
+    const int n = std::min(per_cu, 3) - 1;
+    const double far = std::max(0.0, 1.0 - C.cache / dw_operand_mb(g, prec, M));
+    return cdiv(std::min(kps, M), gemm_bk(prec)) * static_cast<double>(C.slab[n][tc.tile]) * (1.0 + far * C.far[n]) +
+           C.start[tc.tile] + static_cast<double>(C.per_wg[tc.tile]) * per_cu +
+           splits * (C.per_split + C.per_mparam * g.P * 1e-6);
+}
+
+// Tile and splits of the weight gradient for M samples, by rule: the split and
+// the tile's height fix the order of the sums, so a choice by timing would let
+// near ties change an update's result from one process to the next (2048 and
+// 12288 samples of [512, 256, 128] with 48 inputs: 2 to 5 % between the first four).
+// The cheapest by dw_cost.  From 550 MB of bf16 operands on, where 128 x 128
+// tiles are bound by memory either way and half and full rounds take the same
+// time within what the buffers' places change it (0.91 to 1.07 over 20 networks
+// and sizes, 180 against 192 us for 73728 samples of [512, 256, 128] with 235
+// inputs), the half round, which writes half the partials, if it fills seven
+// eighths of the CUs and no paired launch (pair_dw_tiles) takes the full one.
+TileChoice dw_rule(const NetLayout &g, Precision prec, int M, bool pairs_full_round) {
+    TileChoice best;
+    double low = 1e30;
+    for (int tile = 0; tile < kNumTileShapes; ++tile)
+        for (int rounds : {1, 2, 4}) {
+            TileChoice tc;
+            tc.tile = tile;
+            tc.rounds = rounds;
+            const double cost = dw_cost(g, prec, M, tc);
+            if (cost < low) {
+                low = cost;
+                best = tc;
+            }
+        }
+    if (prec == kBF16 && !pairs_full_round && dw_on_fast_path(prec, M) && dw_operand_mb(g, prec, M) > 550.0) {
+        TileChoice half;
+        half.rounds = 1;
+        int splits, kps;
+        dw_splits(g, prec, M, half.tile, half.rounds, splits, kps);
+        const int wgs = dw_tiles(g, half.tile) * splits;
+        constexpr int cus = kResidentSlots / 2;
+        if (wgs <= cus && 8 * wgs >= 7 * cus) best = half;
+    }
+    return best;
+}
+
 WsPlan plan_workspace(const NetLayout &g, Precision prec, int N, int T, int M) {
     WsPlan w;
     w.esz = prec == kBF16 ? 2 : 4;
@@ -392,11 +487,6 @@ int check_device() {
 // ----------------------------------------------------------- tile choices
 // GEMM launch sites of one mini-batch step (or one rollout step).
 enum Site { kSiteFwd = 0, kSiteDx = kMaxHidden, kSiteDw = 2 * kMaxHidden, kNumSites = 2 * kMaxHidden + 1 };
-
-struct TileChoice {
-    int tile = kTile128x128;
-    int rounds = 2;  // weight-gradient splits: half rounds of resident workgroups (1, 2 or 4)
-};
 
 struct Tuning {
     TileChoice site[kNumSites];
@@ -643,10 +733,9 @@ void pair_dw_tiles(GemmArgs &args, int group, Precision prec) {
 
 // kps_layer (optional, per layer 0..L, both networks): samples per split in
 // place of the run's own choice where positive.  Problems are added network
-// by network, layer by layer: problem net * (L + 1) + l.  pair: pair the tiles
-// where pair_dw_tiles does.
+// by network, layer by layer: problem net * (L + 1) + l.
 DwPlan build_dw(const ppo_ctx *c, const WsPlan &w, void *ws, int M, const TileChoice &tc,
-                const int *kps_layer = nullptr, bool pair = true) {
+                const int *kps_layer = nullptr) {
     const NetLayout &g = c->g;
     const int L = g.L;
     DwPlan d;
@@ -712,15 +801,21 @@ DwPlan build_dw(const ppo_ctx *c, const WsPlan &w, void *ws, int M, const TileCh
         }
     }
     ++d.n_launch;
-    if (d.n_launch == 1 && !kps_layer && pair) pair_dw_tiles(d.launch[0], L + 1, c->prec);
+    if (d.n_launch == 1 && !kps_layer) pair_dw_tiles(d.launch[0], L + 1, c->prec);
     plan_reduce(d.red);
     return d;
 }
 
+// dw_rule's choice for this context and workspace.
+TileChoice dw_choice(const ppo_ctx *c, const WsPlan &w, void *ws, int M) {
+    const bool pairs = build_dw(c, w, ws, M, TileChoice{}).launch[0].tile == kTile256x128;
+    return dw_rule(c->g, c->prec, M, pairs);
+}
+
 // ------------------------------------------------------------- autotuner
-// Each GEMM launch site picks its tile shape (and, for the weight
-// gradients, its split rounds) by timing every candidate with HIP events on
-// the caller's stream the first time a row count is seen.  Candidates touch
+// Each GEMM launch site picks its tile shape (the weight gradients among the
+// tiles that keep their rule's split) by timing every candidate with HIP
+// events on the caller's stream the first time a row count is seen.  Candidates touch
 // only the workspace regions they would write anyway, so the timing launches
 // leave no trace.  Results are kept per context and row count, and in the
 // file named by PPO_TUNE_CACHE if set; PPO_AUTOTUNE=0 keeps the defaults.
@@ -855,50 +950,57 @@ int ensure_tuned(const ppo_ctx *cc, const ppo_params *p, const WsPlan &w, void *
                     }
                 }
             }
-            // each candidate is timed with the reduction of its partials (no
-            // rate update), since fewer splits trade GEMM parallelism for
-            // fewer partial bytes
-            float best = 1e30f;
+            // The rule fixes the order of the sums (splits and tile height); what
+            // is left to timing is the tile's width.  Each candidate is timed as
+            // it will run, with the reduction of its partials (no rate update).
+            const TileChoice rule = dw_choice(c, w, ws, rows);
+            int rule_splits, rule_kps;
+            dw_splits(g, prec, rows, rule.tile, rule.rounds, rule_splits, rule_kps);
+            std::vector<TileChoice> same;
             for (int tile = 0; tile < kNumTileShapes; ++tile)
                 for (int rounds : {1, 2, 4}) {
+                    int splits, kps;
+                    dw_splits(g, prec, rows, tile, rounds, splits, kps);
+                    if (tile_rows(tile) != tile_rows(rule.tile) || kps != rule_kps) continue;
                     TileChoice tc;
                     tc.tile = tile;
                     tc.rounds = rounds;
-                    // Timed as plain tiles, so that pairing, which changes no
-                    // result, leaves a clear choice of the split, which does,
-                    // as it is.  Near ties go to the candidate that will run
-                    // paired ([1024, 512, 256], 49152 samples: 312-314 us with
-                    // four splits against 314-320 with two, and 250 paired).
-                    DwPlan d = build_dw(c, w, ws, rows, tc, nullptr, false);
-                    ReduceArgs &red = d.red;
-                    red.grad = grad_scratch;
-                    red.sumsq_partials = reinterpret_cast<double *>(wsp(ws, w.sumsq));
-                    red.loss_partials = reinterpret_cast<const float *>(wsp(ws, w.loss_part));
-                    red.n_loss = head_loss_blocks(rows);
-                    red.loss_width = head_loss_partial_width(g.A);
-                    red.A = g.A;
-                    red.logstd_offset = g.logstd;
-                    red.loss_sums = reinterpret_cast<float *>(wsp(ws, w.loss_sums));
-                    red.inv_m = 1.0f / static_cast<float>(rows);
-                    red.lr = nullptr;
-                    float ms = 0.0f;
-                    PPO_HIP(time_launch(
-                                s,
-                                [&] {
-                                    hipError_t r = hipSuccess;
-                                    for (int i = 0; i < d.n_launch && r == hipSuccess; ++i)
-                                        r = launch_gemm(prec, 1, 1, kEpiPartial, d.launch[i], s);
-                                    if (r == hipSuccess && grad_scratch) r = launch_grad_reduce(red, s);
-                                    return r;
-                                },
-                                reps, ms),
-                            "autotune weight gradient");
-                    if (build_dw(c, w, ws, rows, tc).launch[0].tile == kTile256x128) ms *= 0.96f;
-                    if (ms < best) {
-                        best = ms;
-                        t.site[kSiteDw] = tc;
-                    }
+                    same.push_back(tc);
+                    break;   // other rounds of this tile are the same launch
                 }
+            t.site[kSiteDw] = rule;
+            float best = 1e30f;
+            for (const TileChoice &tc : same) {
+                if (same.size() == 1) break;
+                DwPlan d = build_dw(c, w, ws, rows, tc);
+                ReduceArgs &red = d.red;
+                red.grad = grad_scratch;
+                red.sumsq_partials = reinterpret_cast<double *>(wsp(ws, w.sumsq));
+                red.loss_partials = reinterpret_cast<const float *>(wsp(ws, w.loss_part));
+                red.n_loss = head_loss_blocks(rows);
+                red.loss_width = head_loss_partial_width(g.A);
+                red.A = g.A;
+                red.logstd_offset = g.logstd;
+                red.loss_sums = reinterpret_cast<float *>(wsp(ws, w.loss_sums));
+                red.inv_m = 1.0f / static_cast<float>(rows);
+                red.lr = nullptr;
+                float ms = 0.0f;
+                PPO_HIP(time_launch(
+                            s,
+                            [&] {
+                                hipError_t r = hipSuccess;
+                                for (int i = 0; i < d.n_launch && r == hipSuccess; ++i)
+                                    r = launch_gemm(prec, 1, 1, kEpiPartial, d.launch[i], s);
+                                if (r == hipSuccess && grad_scratch) r = launch_grad_reduce(red, s);
+                                return r;
+                            },
+                            reps, ms),
+                        "autotune weight gradient");
+                if (ms < best) {
+                    best = ms;
+                    t.site[kSiteDw] = tc;
+                }
+            }
         }
         tune_file_store(key, t);
     }
@@ -2296,6 +2398,34 @@ int ppo_update_batched(ppo_ctx *const *ctxs, int32_t R, void *stream, const ppo_
         g_batched_order.push_back(key);
     }
     PPO_HIP(hipGraphLaunch(exec, s), "hipGraphLaunch");
+    return PPO_OK;
+}
+
+int ppo_weight_grad_plan(const ppo_ctx *c, int32_t rows, int32_t tile, int32_t rounds, int32_t *plan,
+                         int32_t capacity) {
+    if (!c) return fail(PPO_E_INVAL, "ctx is NULL");
+    if (!plan) return fail(PPO_E_INVAL, "plan is NULL");
+    if (capacity < 6) return fail(PPO_E_SHAPE, "capacity %d < 6", capacity);
+    if (rows < 1) return fail(PPO_E_SHAPE, "rows = %d must be positive", rows);
+    if (tile < -1 || tile >= kNumTileShapes) return fail(PPO_E_INVAL, "tile %d", tile);
+    if (tile >= 0 && rounds != 1 && rounds != 2 && rounds != 4) return fail(PPO_E_INVAL, "rounds %d", rounds);
+    const WsPlan w = plan_workspace(c->g, c->prec, 0, 0, rows);
+    TileChoice tc;
+    if (tile < 0) {
+        tc = dw_choice(c, w, nullptr, rows);
+    } else {
+        tc.tile = tile;
+        tc.rounds = rounds;
+    }
+    const DwPlan d = build_dw(c, w, nullptr, rows, tc);
+    int workgroups = 0;
+    for (int i = 0; i < d.n_launch; ++i) workgroups += d.launch[i].total_tiles;
+    plan[0] = tc.tile;
+    plan[1] = tc.rounds;
+    plan[2] = d.launch[0].p[0].splits;
+    plan[3] = d.launch[0].p[0].kps;
+    plan[4] = workgroups;
+    plan[5] = d.launch[0].tile == kTile256x128 ? 1 : 0;
     return PPO_OK;
 }
 
