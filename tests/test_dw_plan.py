@@ -55,6 +55,27 @@ def test_plans_cover_the_samples():
                 assert p["workgroups"] % s == 0
 
 
+@pytest.mark.parametrize("D,H,M", [(48, (64, 64), 24576), (235, (128, 128), 49152), (300, (128, 128), 98304),
+                                   (235, (64, 64), 4096), (235, (512, 256, 128), 1024), (48, (512, 384, 256), 8192),
+                                   (235, (1024, 512, 128), 8192)])
+def test_narrow_layers_never_pair(D, H, M):
+    """A layer of fewer than 256 outputs leaves paired tiles mostly empty."""
+    ctx = ppo.Context(D, 12, H, "bf16")
+    for rounds in (1, 2, 4):
+        assert not ctx.weight_grad_plan(M, 0, rounds)["paired"]
+    assert not ctx.weight_grad_plan(M)["paired"]
+
+
+@pytest.mark.parametrize("D,H,M,splits", [(235, (1024, 512, 256), 49152, 4), (235, (1024, 512, 256), 1000, 4),
+                                          (129, (1024, 512, 256), 4104, 4), (256, (1024, 512, 256), 8192, 4),
+                                          (48, (512, 512, 256), 24576, 8), (300, (1024, 1024, 512), 98304, 2)])
+def test_wide_layers_pair(D, H, M, splits):
+    plan = ppo.Context(D, 12, H, "bf16").weight_grad_plan(M, 0, 2)
+    assert plan["paired"] and plan["splits"] == splits and 224 <= plan["workgroups"] <= 256
+    assert not ppo.Context(D, 12, H, "fp32").weight_grad_plan(M, 0, 2)["paired"]
+    assert not ppo.Context(D, 12, H, "bf16").weight_grad_plan(M + 1, 0, 2)["paired"]   # off the buffer-load path
+
+
 def test_bad_arguments():
     lib, ctx = ppo.load(), ppo.Context(48, 12, (64, 64), "bf16")
     arr = (ctypes.c_int32 * 6)()
