@@ -394,9 +394,11 @@ int ppo_weight_grad_plan(const ppo_ctx *ctx, int32_t rows, int32_t tile, int32_t
  * ppo_gemm_check), choices[2 s + 1] = weight-gradient splits in half rounds
  * of resident workgroups (1, 2 or 4; 2 elsewhere), for sites
  * s = 0..3 forward layer s, 4..7 input gradient of layer s - 4, 8 weight
- * gradients.  capacity >= 18.  The defaults (0, 2) where inference ran in one
- * launch although ppo_fused_infer_shape reports none.  PPO_E_SHAPE if nothing
- * was tuned yet. */
+ * gradients.  capacity >= 18.  PPO_E_SHAPE if nothing was tuned yet.  For row
+ * counts whose inference ran in one launch that ppo_fused_infer_shape does not
+ * report (ppo_infer_block does) it still answers, as for the tuned GEMMs which
+ * that launch replaced, but with (0, 2) throughout: no tile was chosen or
+ * launched (the last 64 such row counts). */
 int ppo_ctx_tuning(const ppo_ctx *ctx, int32_t rows, int32_t update, int32_t *choices, int32_t capacity);
 
 /* Block shape of the fused per-sample pass that bf16 update steps of this
@@ -413,8 +415,16 @@ int ppo_fused_shape(const ppo_ctx *ctx, int32_t *rows, int32_t *threads);
  * more, shorter workgroups finish it sooner.  Both 0 also for networks outside
  * this block that inference runs in a single launch of another one (narrow
  * widths such as [64, 64], wide first layers such as [1024, 512, 256], input
- * widths that are no multiple of 16).  Host only. */
+ * widths that, padded to a multiple of 8, are none of 16): see
+ * ppo_infer_block.  Host only. */
 int ppo_fused_infer_shape(const ppo_ctx *ctx, int32_t *rows, int32_t *threads);
+
+/* Block of the one launch in which ppo_rollout_infer runs this network:
+ * *rows environments per workgroup of *threads threads, whichever of the
+ * blocks it is; both 0 when the layer-by-layer kernels run.  Reflects PPO_FUSED,
+ * PPO_FUSED_ROWS and PPO_FUSED_THREADS as set now; calls with more than 2^31
+ * bytes of observations fall back all the same.  Host only. */
+int ppo_infer_block(const ppo_ctx *ctx, int32_t *rows, int32_t *threads);
 
 /* Terrain seen by the height scan: a height field on a uniform grid and the
  * scan pattern.  Cell (i, j) of `height` [nx, ny] (row-major, float32) is the

@@ -130,7 +130,9 @@ class Context:
     TILE_NAMES = ("128x128", "64x128", "128x64", "64x64")
 
     def tuning(self, rows: int, update: bool) -> Dict[str, object]:
-        """Tile choices the autotuner recorded for `rows` GEMM rows."""
+        """Tile choices the autotuner recorded for `rows` GEMM rows.  Where
+        infer_block() is not (0, 0) inference launches no tiles: the defaults that
+        some of those networks get here stand for none."""
         arr = (ctypes.c_int32 * 18)()
         check(_lib().ppo_ctx_tuning(self.handle, rows, int(update), arr, 18))
         out = {}
@@ -157,9 +159,17 @@ class Context:
         return r.value, t.value
 
     def fused_infer_shape(self) -> Tuple[int, int]:
-        """(environments, threads) per workgroup of bf16 fused inference, or (0, 0)."""
+        """(environments, threads) per workgroup of bf16 inference in its general
+        block, or (0, 0); infer_block() also reports the other blocks."""
         r, t = ctypes.c_int32(0), ctypes.c_int32(0)
         check(_lib().ppo_fused_infer_shape(self.handle, ctypes.byref(r), ctypes.byref(t)))
+        return r.value, t.value
+
+    def infer_block(self) -> Tuple[int, int]:
+        """(environments, threads) per workgroup of the one launch that inference
+        of this network takes, or (0, 0) when it runs layer by layer."""
+        r, t = ctypes.c_int32(0), ctypes.c_int32(0)
+        check(_lib().ppo_infer_block(self.handle, ctypes.byref(r), ctypes.byref(t)))
         return r.value, t.value
 
     def keep_packed(self, enable: bool = True) -> None:

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -11,7 +13,6 @@
 #include <cstring>
 #include <map>
 #include <mutex>
-#include <set>
 #include <string>
 #include <vector>
 
@@ -505,7 +506,12 @@ struct ppo_ctx {
     std::map<std::vector<uint64_t>, hipGraphExec_t> graphs;
     std::vector<std::vector<uint64_t>> graph_order;  // insertion order for eviction
     std::map<int, Tuning> tuned;                      // GEMM rows -> measured tile choices
-    std::set<int> untiled;   // rows whose inference ran as a narrow, wide or odd-width pass
+    // The last row counts whose inference ran in one launch that
+    // ppo_fused_infer_shape does not report (0: free): ppo_ctx_tuning answers for
+    // them, as it did when those networks ran tuned GEMMs.  Without a lock: an
+    // inference call only looks its count up.
+    std::array<std::atomic<int32_t>, 64> untiled{};
+    std::atomic<uint32_t> untiled_next{0};
     bool keep_packed = false;                         // PPO_OPT_KEEP_PACKED
 };
 
@@ -530,6 +536,18 @@ Weights gemm_weights(const ppo_ctx *c, const ppo_params *p) {
         }
     }
     return w;
+}
+
+bool ran_untiled(const ppo_ctx *c, int rows) {
+    for (const auto &r : c->untiled)
+        if (r.load(std::memory_order_relaxed) == rows) return rows > 0;
+    return false;
+}
+
+void note_untiled(ppo_ctx *c, int rows) {
+    if (ran_untiled(c, rows)) return;
+    const uint32_t at = c->untiled_next.fetch_add(1, std::memory_order_relaxed);
+    c->untiled[at % c->untiled.size()].store(rows, std::memory_order_relaxed);
 }
 
 char *wsp(void *ws, const Region &r) { return static_cast<char *>(ws) + r.off; }
@@ -1562,11 +1580,7 @@ int ppo_rollout_infer(const ppo_ctx *c, void *stream, const ppo_params *p, const
         PPO_HIP(launch_fused_infer(a, s), "fused inference");
         // ppo_fused_infer_shape reports the general pass alone; for the others
         // ppo_ctx_tuning keeps answering
-        if (fsh.per_cu < 0 || fsh.threads < 256 || w.kpad % 16 != 0) {
-            ppo_ctx *cc = const_cast<ppo_ctx *>(c);
-            std::lock_guard<std::mutex> lk(cc->mu);
-            cc->untiled.insert(N);
-        }
+        if (fsh.per_cu < 0 || fsh.threads < 256 || w.kpad % 16 != 0) note_untiled(const_cast<ppo_ctx *>(c), N);
         return PPO_OK;
     }
     note_ws_used(ws, ws_bytes);
@@ -2442,7 +2456,7 @@ int ppo_ctx_tuning(const ppo_ctx *c, int32_t rows, int32_t update, int32_t *choi
     std::lock_guard<std::mutex> lk(cc->mu);
     auto it = cc->tuned.find(update ? -rows : rows);
     const bool known = it != cc->tuned.end();
-    if (!known && (update || !cc->untiled.count(rows)))
+    if (!known && (update || !ran_untiled(cc, rows)))
         return fail(PPO_E_SHAPE, "no tile choice recorded for %d rows", rows);
     const Tuning t = known ? it->second : Tuning{};
     for (int i = 0; i < kNumSites; ++i) {
@@ -2482,6 +2496,18 @@ int ppo_fused_shape(const ppo_ctx *c, int32_t *rows, int32_t *threads) {
 
 int ppo_fused_infer_shape(const ppo_ctx *c, int32_t *rows, int32_t *threads) {
     return fused_shape_query(c, rows, threads, true);
+}
+
+int ppo_infer_block(const ppo_ctx *c, int32_t *rows, int32_t *threads) {
+    if (!c) return fail(PPO_E_INVAL, "ctx is NULL");
+    if (!rows || !threads) return fail(PPO_E_INVAL, "rows or threads is NULL");
+    // parameters that start 16-byte aligned, as every call requires
+    ppo_params p{};
+    const WsPlan w = plan_workspace(c->g, c->prec, 1, 0, 0);
+    const FusedShape sh = fused_shape_for(c, &p, w, 1, true);
+    *rows = sh.rows;
+    *threads = sh.threads;
+    return PPO_OK;
 }
 
 int ppo_assemble_obs(const ppo_ctx *c, void *stream, const float *proprio, int32_t n_proprio, const float *base,
