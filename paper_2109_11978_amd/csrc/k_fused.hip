@@ -1452,7 +1452,7 @@ __device__ __forceinline__ void infer_head(const FusedArgs &a, int net, const ui
 // iteration, 1) for the g-th group of four actions of environment n, two
 // Box-Muller pairs per draw) and its log-density
 // sum_j (-eps_j^2 / 2 - log sigma_j) - (A / 2) log(2 pi); for the critic the
-// value.  Same draws, formulas and float64 log-density as the
+// value.  Same draws, formulas and compensated float32 log-density as the
 // layer-by-layer sampling kernel; only the output layer's summation order
 // differs.
 // SEL: the hidden layers round as the layer-by-layer GEMM epilogues do (elu_select).
@@ -1479,8 +1479,8 @@ void fused_infer_kernel(const FusedArgs a) {
     const int xp = a.kpad + 8;
     ActorNoise noise{};
     {
-        // output-layer weights, output biases, log-std and hidden biases in one
-        // round of buffer loads, then the LDS stores (as in the update pass)
+        // output-layer weights, output biases and hidden biases in one round of
+        // buffer loads, then the LDS stores (as in the update pass)
         // 16-byte loads: the output-layer weights and the hidden biases are
         // 16-byte aligned, rows of a multiple of 32 elements
         constexpr int UW = 4;   // 4-element chunks of the output-layer weights per thread
@@ -1499,9 +1499,7 @@ void fused_infer_kernel(const FusedArgs a) {
             vb[l] = __builtin_amdgcn_raw_buffer_load_b128(rb, 4 * tid < H ? tid * 16 : kOutside, 0, 0);
         }
         const __amdgpu_buffer_rsrc_t ro = make_rsrc(N.bout, static_cast<long long>(n_out) * 4);
-        const __amdgpu_buffer_rsrc_t rl = make_rsrc(a.logstd, static_cast<long long>(A) * 4);
         const float vo = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, tid < n_out ? tid * 4 : kOutside, 0, 0));
-        const float vl = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rl, tid < A ? tid * 4 : kOutside, 0, 0));
         // the observation rows are the block's own (no index list): their loads
         // go out behind the weight loads, so the prologue waits for memory once
         gather_rows<R, NT>(a, nullptr, rows, x, xp, wave, lane, m0, [&]() {
@@ -1516,10 +1514,7 @@ void fused_infer_kernel(const FusedArgs a) {
 #pragma unroll
         for (int l = 0; l < kMaxHidden; ++l)
             if (l < L && 4 * tid < a.H[l]) *reinterpret_cast<u32x4 *>(s_bias + a.bias_off[l] + 4 * tid) = vb[l];
-        if (tid < kFusedMaxAct) {
-            s_head[tid] = tid < n_out ? vo : 0.0f;
-            s_head[kFusedMaxAct + tid] = tid < A ? vl : 0.0f;
-        }
+        if (tid < kFusedMaxAct) s_head[tid] = tid < n_out ? vo : 0.0f;
         for (int q = nw + tid; q < kFusedMaxAct * Hl; q += NT) {
             const int j = q / Hl;
             w_out[j * WP + (q - j * Hl)] = 0.0f;
@@ -1646,8 +1641,8 @@ void wide_infer_kernel(const FusedArgs a) {
     const FusedNet &N = a.net[net];
     ActorNoise noise{};
     {
-        // hidden biases (16-byte aligned, at most 4 NT wide), output biases and
-        // log-std, and the block's observation rows, in one round of loads
+        // hidden biases (16-byte aligned, at most 4 NT wide), output biases and the
+        // block's observation rows, in one round of loads
         u32x4 vb[kMaxHidden];
 #pragma unroll
         for (int l = 0; l < kMaxHidden; ++l) {
@@ -1656,9 +1651,7 @@ void wide_infer_kernel(const FusedArgs a) {
             vb[l] = __builtin_amdgcn_raw_buffer_load_b128(rb, 4 * tid < H ? tid * 16 : kOutside, 0, 0);
         }
         const __amdgpu_buffer_rsrc_t ro = make_rsrc(N.bout, static_cast<long long>(n_out) * 4);
-        const __amdgpu_buffer_rsrc_t rl = make_rsrc(a.logstd, static_cast<long long>(a.A) * 4);
         const float vo = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, tid < n_out ? tid * 4 : kOutside, 0, 0));
-        const float vl = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rl, tid < a.A ? tid * 4 : kOutside, 0, 0));
         gather_rows<R, NT>(a, nullptr, rows, reinterpret_cast<uint16_t *>(lds + a.lds_x), a.kpad + 8, wave, lane, m0,
                            [&]() {
                                if (net == 0) noise = actor_noise<NT / R>(a, m0, rows);
@@ -1666,10 +1659,7 @@ void wide_infer_kernel(const FusedArgs a) {
 #pragma unroll
         for (int l = 0; l < kMaxHidden; ++l)
             if (l < a.L && 4 * tid < a.H[l]) *reinterpret_cast<u32x4 *>(s_bias + a.bias_off[l] + 4 * tid) = vb[l];
-        if (tid < kFusedMaxAct) {
-            s_head[tid] = tid < n_out ? vo : 0.0f;
-            s_head[kFusedMaxAct + tid] = tid < a.A ? vl : 0.0f;
-        }
+        if (tid < kFusedMaxAct) s_head[tid] = tid < n_out ? vo : 0.0f;
     }
     __syncthreads();
     // the critic's weights come in the split layout (bf16 and residual fragments)
@@ -1790,7 +1780,7 @@ size_t wide_layout(int L, const int *H, int kpad, FusedArgs *a) {
         bias_off[l] = static_cast<int>(nb);
         nb += H[l];
     }
-    const size_t total = region + nb * 4 + 2 * kFusedMaxAct * 4;
+    const size_t total = region + nb * 4 + kFusedMaxAct * 4;
     if (total > static_cast<size_t>(kMaxLdsBytes)) return 0;
     if (a) {
         a->lds_x = static_cast<int>(x_off);
