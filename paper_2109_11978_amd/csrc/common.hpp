@@ -219,6 +219,7 @@ struct FusedArgs {
     int defer_in;                     // the loss inputs load during the first layer after the streamed pair
     int vec_out;                      // inference: actions and means by 16-byte stores (A % 4 == 0, 16-byte aligned)
     int bias_off[kMaxHidden];         // floats into the staged biases
+    int noise_first;                  // inference: the actor's noise behind the observation loads, else before the head
 };
 // Samples per workgroup and threads per workgroup of the fused pass for this
 // network shape ({0, 0} when it does not apply: hidden widths that do not

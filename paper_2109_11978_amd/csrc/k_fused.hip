@@ -418,15 +418,22 @@ __device__ inline void copy_out(const uint16_t *src, int pitch, uint16_t *dst, i
 // LDS, zero-padded to kpad columns and zero past the last valid row.  Wave w
 // takes rows w, w + NW, ...; its lanes take consecutive 16-byte chunks of
 // those rows (coalesced), four loads in flight per lane (out-of-range ones
-// read zero).
+// read zero).  hook: work that fits in the first loads' latency.  The first
+// round then stands before the loop: in the loop's first trip the compiler moves
+// what the hook computes in front of the loop, ahead of the loads.  With a hook,
+// LoadsFirst if there is no work, a round's loads also go out together; without
+// one the compiler puts some behind the first ones' use.
+struct LoadsFirst {
+    __device__ void operator()() const {}
+};
 template <int R, int NT, class Hook = NoHook>
 __device__ inline void gather_rows(const FusedArgs &a, const int *s_rows, int rows, uint16_t *x, int pitch,
                                    int wave, int lane, int m0 = 0, const Hook &hook = Hook()) {
-    // work that fits in the first loads' latency
-    auto meanwhile = [&](int t0) {
-        if constexpr (!std::is_same<Hook, NoHook>::value) {
+    constexpr bool HOOKED = !std::is_same<Hook, NoHook>::value;
+    auto between = [&](auto &&meanwhile) {
+        if constexpr (HOOKED) {
             __builtin_amdgcn_sched_barrier(0);
-            if (t0 == 0) hook();
+            meanwhile();
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -440,7 +447,7 @@ __device__ inline void gather_rows(const FusedArgs &a, const int *s_rows, int ro
         const int n4 = a.kpad >> 2;         // 4-element chunks per row (padded)
         const int d4 = a.D >> 2;
         const int total = PER_WAVE * n4;    // chunks per wave
-        for (int t0 = 0; t0 < total; t0 += V * 64) {
+        auto round = [&](int t0, auto &&meanwhile) {
             float4 v[V];
 #pragma unroll
             for (int u = 0; u < V; ++u) {
@@ -453,7 +460,7 @@ __device__ inline void gather_rows(const FusedArgs &a, const int *s_rows, int ro
                 v[u] = make_float4(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]),
                                    __uint_as_float(w[3]));
             }
-            meanwhile(t0);
+            between(meanwhile);
 #pragma unroll
             for (int u = 0; u < V; ++u) {
                 const int t = t0 + 64 * u + lane;
@@ -464,7 +471,9 @@ __device__ inline void gather_rows(const FusedArgs &a, const int *s_rows, int ro
                         u32x2{pack2(v[u].x, v[u].y), pack2(v[u].z, v[u].w)};
                 }
             }
-        }
+        };
+        if constexpr (HOOKED) round(0, hook);
+        for (int t0 = HOOKED ? V * 64 : 0; t0 < total; t0 += V * 64) round(t0, NoHook());
         return;
     }
     // rows at any alignment: each lane loads one 16-byte aligned chunk of
@@ -479,7 +488,7 @@ __device__ inline void gather_rows(const FusedArgs &a, const int *s_rows, int ro
     const int n4 = (a.kpad >> 2) + 1;       // chunks per row
     const int total = PER_WAVE * n4;        // chunks per wave
     const __amdgpu_buffer_rsrc_t ru = make_rsrc(a.obs, (static_cast<long long>(a.B) * a.D * 4 + 15) & ~15LL);
-    for (int t0 = 0; t0 < total; t0 += V * 64) {
+    auto round = [&](int t0, auto &&meanwhile) {
         u32x4 w[V];
         int e0[V];
 #pragma unroll
@@ -492,7 +501,7 @@ __device__ inline void gather_rows(const FusedArgs &a, const int *s_rows, int ro
             const bool ok = t0 + 64 * u + lane < total && i < rows;
             w[u] = __builtin_amdgcn_raw_buffer_load_b128(ru, ok ? ((e0[u] >> 2) + c) * 16 : kOutside, 0, 0);
         }
-        meanwhile(t0);
+        between(meanwhile);
 #pragma unroll
         for (int u = 0; u < V; ++u) {
             const int t = t0 + 64 * u + lane;
@@ -507,7 +516,9 @@ __device__ inline void gather_rows(const FusedArgs &a, const int *s_rows, int ro
                     x[i * pitch + k] = static_cast<uint16_t>(k < a.D ? bf16_bits(__uint_as_float(w[u][q])) : 0u);
             }
         }
-    }
+    };
+    if constexpr (HOOKED) round(0, hook);
+    for (int t0 = HOOKED ? V * 64 : 0; t0 < total; t0 += V * 64) round(t0, NoHook());
 }
 
 // Sum over the KP adjacent lanes of a sample (KP = 4, 8 or 16) with DPP lane
@@ -1324,6 +1335,7 @@ __global__ __launch_bounds__(256) void pack_frags_kernel(const FragArgs a) {
 // [256, 128, 64]): two waves.  One launch instead of five or six, each of
 // which is a launch's latency at these sizes: [64, 64] over 64 environments
 // 29.5 -> 11.2 us a call, over 20000 41.4 -> 17.7 us.
+constexpr int kNoiseFirstBlocks = 256;   // one per CU
 constexpr int kNarrowRows = 32, kNarrowThreads = 128;
 // per_cu of the wide pass's shape (wide_infer_kernel)
 constexpr int kWidePass = -1;
@@ -1332,10 +1344,10 @@ constexpr int kWidePass = -1;
 // 4, at most 4 groups) with Philox counter (n groups + kq, t, iteration, 1) and
 // two Box-Muller pairs, and loads the sigmas of its four actions; the
 // environment's first lane sums the log-density over the actions in order and
-// writes it.  Needs no network output, so it runs while the observations load.
-// In the head, after the means, it was 8K of the 34K cycles of an actor's block
-// (4.7K of them the log-density's chain of additions); 24 steps of 4096
-// environments with D = 48 and [128, 64, 32] took 427 us so and take 413.
+// writes it.  Needs no network output: 8K of the 34K cycles of an actor's block
+// (4.7K of them the log-density's chain of additions), which run while the
+// observations load where a block has nothing else to do (noise_first, see
+// launch_fused_infer) and before the head otherwise.
 struct ActorNoise {
     float eps[4], sig[4];
 };
@@ -1372,6 +1384,12 @@ __device__ __forceinline__ ActorNoise actor_noise(const FusedArgs &a, int m0, in
 #pragma unroll
     for (int q = 0; q < 4; ++q) z.sig[q] = expf(ls[q]);
     return z;
+}
+
+// The noise as a gather's hook.
+template <int KP>
+__device__ __forceinline__ auto draw_noise(const FusedArgs &a, int m0, int rows, ActorNoise &noise) {
+    return [&a, m0, rows, &noise]() { noise = actor_noise<KP>(a, m0, rows); };
 }
 
 // Output layer of the block's environments (last hidden layer hl, rows of
@@ -1501,10 +1519,12 @@ void fused_infer_kernel(const FusedArgs a) {
         const __amdgpu_buffer_rsrc_t ro = make_rsrc(N.bout, static_cast<long long>(n_out) * 4);
         const float vo = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, tid < n_out ? tid * 4 : kOutside, 0, 0));
         // the observation rows are the block's own (no index list): their loads
-        // go out behind the weight loads, so the prologue waits for memory once
-        gather_rows<R, NT>(a, nullptr, rows, x, xp, wave, lane, m0, [&]() {
-            if (net == 0) noise = actor_noise<KP>(a, m0, rows);
-        });
+        // go out behind the weight loads.  The critic's blocks take no part in
+        // the noise and keep a gather without it
+        if (net == 0 && a.noise_first)
+            gather_rows<R, NT>(a, nullptr, rows, x, xp, wave, lane, m0, draw_noise<KP>(a, m0, rows, noise));
+        else
+            gather_rows<R, NT>(a, nullptr, rows, x, xp, wave, lane, m0, LoadsFirst());
 #pragma unroll
         for (int u = 0; u < UW; ++u) {
             const int q = 4 * (tid + u * NT);
@@ -1543,6 +1563,7 @@ void fused_infer_kernel(const FusedArgs a) {
         K = H;
     }
 
+    if (net == 0 && !a.noise_first) noise = actor_noise<KP>(a, m0, rows);
     infer_head<KP>(a, net, reinterpret_cast<const uint16_t *>(lds + a.lds_region[L - 1]), w_out, s_head, noise, m0,
                    rows);
 }
@@ -1652,10 +1673,11 @@ void wide_infer_kernel(const FusedArgs a) {
         }
         const __amdgpu_buffer_rsrc_t ro = make_rsrc(N.bout, static_cast<long long>(n_out) * 4);
         const float vo = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ro, tid < n_out ? tid * 4 : kOutside, 0, 0));
-        gather_rows<R, NT>(a, nullptr, rows, reinterpret_cast<uint16_t *>(lds + a.lds_x), a.kpad + 8, wave, lane, m0,
-                           [&]() {
-                               if (net == 0) noise = actor_noise<NT / R>(a, m0, rows);
-                           });
+        uint16_t *x = reinterpret_cast<uint16_t *>(lds + a.lds_x);
+        if (net == 0 && a.noise_first)
+            gather_rows<R, NT>(a, nullptr, rows, x, a.kpad + 8, wave, lane, m0, draw_noise<NT / R>(a, m0, rows, noise));
+        else
+            gather_rows<R, NT>(a, nullptr, rows, x, a.kpad + 8, wave, lane, m0, LoadsFirst());
 #pragma unroll
         for (int l = 0; l < kMaxHidden; ++l)
             if (l < a.L && 4 * tid < a.H[l]) *reinterpret_cast<u32x4 *>(s_bias + a.bias_off[l] + 4 * tid) = vb[l];
@@ -1668,6 +1690,7 @@ void wide_infer_kernel(const FusedArgs a) {
     else
         wide_layers<1>(a, N, lds, s_bias, w_out, n_out, wave, lane);
     if (a.L == 2) __syncthreads();
+    if (net == 0 && !a.noise_first) noise = actor_noise<NT / R>(a, m0, rows);
     infer_head<NT / R>(a, net, reinterpret_cast<const uint16_t *>(lds), w_out, s_head, noise, m0, rows);
 }
 
@@ -2065,6 +2088,13 @@ hipError_t launch_fused_infer(FusedArgs a, hipStream_t s) {
                               : fused_layout(a.L, a.H, a.kpad, a.A, a.R, a.NT, &a);
     if (bytes == 0) return hipErrorInvalidValue;
     a.blocks = fused_blocks(a.M, a.R);
+    // The actor's noise behind the observation loads as long as every block has a
+    // CU to itself: [512, 256, 128] with 48 inputs, 64 environments 15.9 -> 14.6 us
+    // a call against the noise in the head, 4096 of them 18.4 -> 16.4.  With more
+    // blocks another one fills that time, and the values that wait in registers
+    // cost: 20000 environments with 235 inputs 65.7 us with the noise in the head,
+    // 67.0 ahead, 262144 of them 733 and 759.
+    a.noise_first = 2 * a.blocks <= kNoiseFirstBlocks ? 1 : 0;
     // The general block's shapes, then the narrow one, each with the median ELU
     // and with the sign test.  Networks whose input width is no multiple of 16
     // once padded to 8 ran layer by layer before the general block took them, so
