@@ -302,8 +302,8 @@ struct GaeArgs {
     int T, N;
     float gamma, lam;
 };
-int gae_blocks(int N);
-int gae_max_blocks(int N);   // largest gae_blocks of any count up to N (sizes workspaces)
+int gae_blocks(int N, int T);
+int gae_max_blocks(int N);   // largest gae_blocks of any count up to N and any horizon (sizes workspaces)
 // Environments the allocation-free GAE entry point serves (its partials live
 // in a fixed device array of the library).
 constexpr int kGaeNoAllocMaxN = 1 << 21;

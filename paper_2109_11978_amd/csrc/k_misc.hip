@@ -458,7 +458,7 @@ __global__ __launch_bounds__(kHeadThreads) void head_loss_kernel(const HeadLossA
 // per lane in blocks of four waves, 16 steps at a time, with a Welford update
 // (a float64 division) per step and a tree of merges: 4096 x 24 in 8.9 us and
 // the normalisation in 4.7 us, now 5.4 and 3.4; 2^20 x 24 with normalisation
-// 146 us a call, now 121 to 127 (the scan alone 85 us, 5.3 TB/s).
+// 146 us a call, now 125 (gae_shape has what lies between).
 constexpr int kFinalizeThreads = 256;
 
 template <int VEC, int CHUNK, int THREADS>
@@ -1036,19 +1036,44 @@ hipError_t launch_head_loss(Precision prec, const HeadLossArgs &a, hipStream_t s
     return hipGetLastError();
 }
 
-// Blocks of one wave up to 2^16 environments (1024 of them; from there on the
-// chip is full either way and more partials only lengthen the merge), then of
-// four waves: four environments per lane where the rows stay 16-byte aligned
-// (N a multiple of 4) and there are enough of them to fill the chip, else one.
-constexpr int kGaeSmallN = 1 << 16, kGaeVecN = 1 << 17;
-int gae_blocks(int N) {
-    if (N <= kGaeSmallN) return (N + 63) / 64;
-    const int per = N % 4 == 0 && N >= kGaeVecN ? 1024 : 256;
+// The scan's kernel for N environments of T steps.  Times of the scan and its
+// statistics, in us.
+//
+// Few environments: one per lane and blocks of one wave, in the smallest chunk
+// that holds the horizon, since steps past it load its first row again.  Chunks
+// of 8, 16 and 24 against one of 32 for all, 4096 environments: 8 steps 5.6
+// against 7.0, 16 steps 6.4 against 7.4, 24 steps 7.3 against 7.9; 256 and 65536
+// environments gain as much.  Longer horizons go 32 steps at a time.
+// More: one per lane, blocks of four waves, 16 steps at a time.  A horizon of 25
+// to 256 steps is better off so from 49152 environments on (65536 x 128: 28.8
+// against 35.3 in blocks of one wave; 49152 x 64: 17.8 and 18.5; 32768 x 128: 24.9
+// and 23.8), a shorter one from 65536 on (65536 x 24: 10.4 and 10.9).
+// Many: four per lane where the rows stay 16-byte aligned (N a multiple of 4) and
+// the lanes still fill the chip, from 163840 environments on (200000 x 128: 91
+// against 102; 131072 x 128: 79 against 62), from 131072 on up to 96 steps, whose
+// 16 MB rows stay in the memory-side cache.  From 2^18 on four steps at a time,
+// past 64 steps in blocks of one wave: 2^20 x 24 92 against 96 with eight steps,
+// 2^18 x 256 207 against 222, 2^20 x 96 353 against 426.
+struct GaeShape { int vec, chunk, threads; };
+constexpr int kGaeSmallN = 1 << 16;
+GaeShape gae_shape(int N, int T) {
+    if (N <= 3 << 14 || (N <= kGaeSmallN && (T <= 24 || T > 256)))
+        return {1, T <= 8 ? 8 : T <= 16 ? 16 : T <= 24 ? 24 : 32, 64};
+    if (N % 4 == 0 && (N >= 5 << 15 || (N >= 1 << 17 && T <= 96))) {
+        if (N < 1 << 18) return {4, 8, 256};
+        return {4, 4, T <= 64 ? 256 : 64};
+    }
+    return {1, 16, 256};
+}
+
+int gae_blocks(int N, int T) {
+    const GaeShape sh = gae_shape(N, T);
+    const int per = sh.vec * sh.threads;
     return static_cast<int>((static_cast<long long>(N) + per - 1) / per);
 }
 
 int gae_max_blocks(int N) {
-    return N <= kGaeSmallN ? gae_blocks(N) : std::max(kGaeSmallN / 64, static_cast<int>((N + 255LL) / 256));
+    return N <= kGaeSmallN ? (N + 63) / 64 : std::max(kGaeSmallN / 64, static_cast<int>((N + 255LL) / 256));
 }
 
 // Scratch of the allocation-free GAE entry point: the partials (three doubles
@@ -1078,26 +1103,21 @@ hipError_t gae_scratch(double **out) {
     return hipSuccess;
 }
 
-// Steps past the horizon load its first row again, so few environments take
-// the smallest chunk that holds it: chunks of 8, 16 and 24 against one of 32 for
-// all (scan and statistics of 4096 environments): 8 steps 5.6 against 7.0 us,
-// 16 steps 6.4 against 7.4, 24 steps 7.3 against 7.9; 256 and 65536 environments
-// gain as much.  Longer horizons go 32 steps at a time.
 hipError_t launch_gae(const GaeArgs &a, hipStream_t s) {
-    const dim3 grid(gae_blocks(a.N));
-    if (a.N <= kGaeSmallN && a.T <= 8)
-        hipLaunchKernelGGL((gae_kernel<1, 8, 64>), grid, dim3(64), 0, s, a);
-    else if (a.N <= kGaeSmallN && a.T <= 16)
-        hipLaunchKernelGGL((gae_kernel<1, 16, 64>), grid, dim3(64), 0, s, a);
-    else if (a.N <= kGaeSmallN && a.T <= 24)
-        hipLaunchKernelGGL((gae_kernel<1, 24, 64>), grid, dim3(64), 0, s, a);
-    else if (a.N <= kGaeSmallN)
-        hipLaunchKernelGGL((gae_kernel<1, 32, 64>), grid, dim3(64), 0, s, a);
-    else if (a.N % 4 == 0 && a.N >= kGaeVecN)
-        hipLaunchKernelGGL((gae_kernel<4, 8, 256>), grid, dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL((gae_kernel<1, 16, 256>), grid, dim3(256), 0, s, a);
-    return hipGetLastError();
+    static const struct {
+        GaeShape shape;
+        void (*fn)(const GaeArgs);
+    } kernels[] = {{{1, 8, 64}, &gae_kernel<1, 8, 64>},     {{1, 16, 64}, &gae_kernel<1, 16, 64>},
+                   {{1, 24, 64}, &gae_kernel<1, 24, 64>},   {{1, 32, 64}, &gae_kernel<1, 32, 64>},
+                   {{1, 16, 256}, &gae_kernel<1, 16, 256>}, {{4, 8, 256}, &gae_kernel<4, 8, 256>},
+                   {{4, 4, 256}, &gae_kernel<4, 4, 256>},   {{4, 4, 64}, &gae_kernel<4, 4, 64>}};
+    const GaeShape sh = gae_shape(a.N, a.T);
+    for (const auto &k : kernels)
+        if (k.shape.vec == sh.vec && k.shape.chunk == sh.chunk && k.shape.threads == sh.threads) {
+            hipLaunchKernelGGL(k.fn, dim3(gae_blocks(a.N, a.T)), dim3(sh.threads), 0, s, a);
+            return hipGetLastError();
+        }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_adv_finalize(const double *partials, int nparts, float *adv, long long count, double *stats_out,

@@ -1638,8 +1638,8 @@ int validate_gae(const ppo_ctx *c, const float *rewards, const uint8_t *dones, c
     return PPO_OK;
 }
 
-// The scan with its per-block statistics partials in `partials` (gae_blocks(N)
-// x 3 doubles, every entry written before it is read), then the merge and the
+// The scan with its per-block statistics partials in `partials` (gae_blocks(N,
+// T) x 3 doubles, every entry written before it is read), then the merge and the
 // optional normalisation.
 int enqueue_gae(hipStream_t s, const float *rewards, const uint8_t *dones, const uint8_t *timeouts,
                 const float *values, const float *last_values, int32_t T, int32_t N, float gamma, float lam,
@@ -1658,7 +1658,7 @@ int enqueue_gae(hipStream_t s, const float *rewards, const uint8_t *dones, const
     a.gamma = gamma;
     a.lam = lam;
     PPO_HIP(launch_gae(a, s), "gae");
-    PPO_HIP(launch_adv_finalize(a.partials, gae_blocks(N), adv, static_cast<long long>(T) * N, adv_stats, normalize, s),
+    PPO_HIP(launch_adv_finalize(a.partials, gae_blocks(N, T), adv, static_cast<long long>(T) * N, adv_stats, normalize, s),
             "adv_finalize");
     return PPO_OK;
 }

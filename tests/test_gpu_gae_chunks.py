@@ -1,6 +1,5 @@
-"""GAE at every chunk of its one-wave kernels (8, 16, 24 or 32 steps load
-together up to 65536 environments) and around their edges, against the oracle;
-the statistics against float64 NumPy on the kernel's own advantages."""
+"""GAE at every kernel of its rule and around the rule's edges, against the
+oracle; the statistics against float64 NumPy on the kernel's own advantages."""
 import numpy as np
 import pytest
 import torch
@@ -12,9 +11,14 @@ from tests.parity import TOL, assert_close
 
 pytestmark = pytest.mark.gpu
 
+SMALL = [(T, N) for T in (7, 8, 9, 15, 16, 17, 23, 24, 25, 31, 32, 33, 47, 48, 49, 64, 65, 100) for N in (65, 4096)]
+# edges of the rule: 49152, 65536, 131072, 163840 and 262144 environments; 24, 64, 96 and 256 steps
+MEDIUM = [(T, N) for T in (24, 25, 256, 257) for N in (49152, 49153, 65536, 65537)]
+LARGE = [(T, N) for T in (1, 7, 9, 96, 97) for N in (131072, 131076, 131073, 163836, 163840)]
+MANY = [(T, N) for T in (1, 4, 5, 64, 65) for N in (262140, 262144, 263172, 262145)]
 
-@pytest.mark.parametrize("N", [65, 4096])
-@pytest.mark.parametrize("T", [7, 8, 9, 15, 16, 17, 23, 24, 25, 31, 32, 33, 47, 48, 49, 64, 65, 100])
+
+@pytest.mark.parametrize("T,N", SMALL + MEDIUM + LARGE + MANY)
 def test_gae_chunks(T, N):
     d = require_gpu()
     print(f"[gpu-case] gae chunks T={T} N={N}", flush=True)
