@@ -277,12 +277,13 @@ double dw_cost(const NetLayout &g, Precision prec, int M, const TileChoice &tc) 
 // the tile's height fix the order of the sums, so a choice by timing would let
 // near ties change an update's result from one process to the next (2048 and
 // 12288 samples of [512, 256, 128] with 48 inputs: 2 to 5 % between the first four).
-// The cheapest by dw_cost.  From 550 MB of bf16 operands on, where 128 x 128
-// tiles are bound by memory either way and half and full rounds take the same
-// time within what the buffers' places change it (0.91 to 1.07 over 20 networks
-// and sizes, 180 against 192 us for 73728 samples of [512, 256, 128] with 235
-// inputs), the half round, which writes half the partials, if it fills seven
-// eighths of the CUs and no paired launch (pair_dw_tiles) takes the full one.
+// The cheapest by dw_cost.  From 700 MB of bf16 operands on, where 128 x 128
+// tiles are bound by memory either way and half and full rounds differ by no
+// more than the buffers' places do (0.91 to 1.07 over 20 networks and sizes),
+// the half round, which writes half the partials, if it fills seven eighths of
+// the CUs and no paired launch (pair_dw_tiles) takes the full one.  Below, the
+// full round: 174 against 177 us for 73728 samples of [512, 256, 128] with 235
+// inputs (570 MB); at 102400 (790 MB) timings took the half 14 times in 20.
 TileChoice dw_rule(const NetLayout &g, Precision prec, int M, bool pairs_full_round) {
     TileChoice best;
     double low = 1e30;
@@ -297,7 +298,7 @@ TileChoice dw_rule(const NetLayout &g, Precision prec, int M, bool pairs_full_ro
                 best = tc;
             }
         }
-    if (prec == kBF16 && !pairs_full_round && dw_on_fast_path(prec, M) && dw_operand_mb(g, prec, M) > 550.0) {
+    if (prec == kBF16 && !pairs_full_round && dw_on_fast_path(prec, M) && dw_operand_mb(g, prec, M) > 700.0) {
         TileChoice half;
         half.rounds = 1;
         int splits, kps;
