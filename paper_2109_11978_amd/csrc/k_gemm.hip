@@ -783,7 +783,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(const GemmArgs args) 
 // that reads beyond L2 reach.  Here all 240 workgroups run at the same rate,
 // each reads half as much of one operand, and the tiles of one split of one
 // network, which use every operand once, lie on one XCD: 0.91 GB, 235-248 us
-// (the whole epoch 7.50 -> 6.72 ms).  What bounds it now is the LDS: 256
+// (the whole epoch 7.65 -> 6.86 ms).  What bounds it now is the LDS: 256
 // transposing reads per 64 samples at half the LDS rate take 2048 of the
 // loop's 3000 cycles (199 us without the global loads).  So the fragments are
 // read one k-step ahead, across the barrier into the next slab (three
